@@ -133,13 +133,17 @@ sata_status sata_prefill_grouped(const void* q, const void* k, const void* v, sa
  * and the reverse scan with U_t = sum_{T>=t} phi(q_T) (x) h_T gives
  *     dL/dk_t = J_phi(k_t)^T U_t [v_t, 1],   dL/dv_t = (U_t^T phi(k_t))[0:d_v],
  * J_phi being the Jacobian of the feature map; inside a chunk the gradient of
- * f_P(q.k / sqrt(d_k)), f_{P-1}(s) k / sqrt(d_k), is used directly.
+ * f_P(q.k / sqrt(d_k)), f_{P-1}(s) k / sqrt(d_k), is used directly.  Where the
+ * sequence is short for the number of features (an estimate of the two costs
+ * decides), the whole gradient is formed that way, pair by pair, with the same
+ * results up to rounding and whatever the chunk.
  *   q, k  : [B][H][n][d_k], v, dy : [B][H][n][d_v], dtype dt (device)
  *   dq, dk: [B][H][n][d_k], dv : [B][H][n][d_v], dtype dt (device, written)
  * All arithmetic is float32 (the forward is recomputed, not passed in).
  * chunk: 16, 32 or 64; d_k, d_v <= 64 (SATA_ERR_UNSUPPORTED otherwise).
- * Workspace: float32 dL/d[N|Z] for every token (4 (d_v+1) bytes per
- * head-token), one state, and per-segment partial sums of at most 2 GB.
+ * Workspace: pair by pair 12 bytes per head-token; the scans float32 dL/d[N|Z]
+ * for every token (4 (d_v+1) bytes per head-token), one state, and per-segment
+ * partial sums of at most 2 GB.
  * n = 0 writes nothing. */
 sata_status sata_backward(const void* q, const void* k, const void* v, const void* dy, sata_dtype dt,
                           int B, int H, int n, int d_k, int d_v, int P, int chunk,

@@ -154,6 +154,14 @@ hipError_t launch_backward(const void* q, const void* k, const void* v, const vo
                            const BackwardPlan& plan, const PrefillGenericPlan& fwd, float* h, float* state,
                            float* partial, hipStream_t s);
 
+// ---- backward, pair by pair (backward_direct.hip) --------------------------------
+// Gradients for d_k, d_v <= kMaxBackwardDim and 2 <= P <= 8; stat:
+// backward_direct_bytes(BH, n) bytes of scratch, 16-byte aligned.
+size_t backward_direct_bytes(int BH, int n);
+hipError_t launch_backward_direct(const void* q, const void* k, const void* v, const void* dy, void* dq, void* dk,
+                                  void* dv, bool bf16, int BH, int n, int dk_, int dv_, int P, float* stat,
+                                  hipStream_t s);
+
 // ---- helpers -----------------------------------------------------------------
 hipError_t launch_fill_zero(float* p, int64_t count, hipStream_t s);
 

@@ -2,6 +2,7 @@
 // tables and workspaces, and dispatch to the HIP kernels.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -292,6 +293,24 @@ PrefillPath prefill_path(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, 
   return PrefillPath::kFloat32;
 }
 
+// Longest rows of one head that the pair-by-pair kernels address (32-bit byte
+// offsets into a head's tensor, float32 at d = 64).
+constexpr int64_t kMaxDirectTokens = (int64_t)1 << 22;
+
+// Whether the gradients are computed pair by pair (backward_direct.hip) rather
+// than by the scans over the states: c (n / 2 + 256) ps per head-token against
+// a share of the state.  Measured, ns per head-token at n = 4096 against the
+// scans: d = 32, P = 4 bf16 3.4 / 206, d = 16, P = 3 bf16 3.1 / 10, d = 16,
+// P = 4 f32 6.0 / 28.5, d = 64, P = 2 f32 20 / 28.
+bool backward_direct_pays(sata_dtype dt, int n, int d_k, int d_v, int P, int64_t D) {
+  if (P < 2 || n > kMaxDirectTokens) return false;
+  const int tiles = (std::max(d_k, d_v) + 15) / 16;
+  const double pair = (dt == SATA_BF16 ? (tiles <= 2 ? 1.75 : 2.6) : (tiles == 1 ? 3.0 : tiles == 2 ? 3.7 : 10.0)) +
+                      0.3 * std::max(0, P - 4);
+  const double scan = 1.5 + 0.26 * d_k + 0.9e-3 * (double)D * (d_v + 1);
+  return 1.1 * 1e-3 * pair * (0.5 * n + 256.0) <= scan;
+}
+
 // One prefill over BH key/value heads; q and y hold qg query heads per
 // key/value head (head bh's queries start at head bh * qg of q).
 sata_status prefill_dispatch(const void* q, const void* k, const void* v, sata_dtype dt, int BH, int n, int d_k,
@@ -532,6 +551,14 @@ sata_status sata_backward(const void* q, const void* k, const void* v, const voi
   if (!sata::plan_backward(D, BH, n, d_k, d_v, P, chunk, kMaxBackwardWorkspace, &plan, &fwd))
     return fail(SATA_ERR_UNSUPPORTED, "no backward slice fits on chip for d_k=%d d_v=%d chunk=%d", d_k, d_v, chunk);
   hipStream_t s = (hipStream_t)stream;
+  if (backward_direct_pays(dt, n, d_k, d_v, P, D)) {
+    void* ws = nullptr;
+    if ((st = get_workspace(sata::backward_direct_bytes(BH, n), s, &ws)) != SATA_OK) return st;
+    hipError_t e = sata::launch_backward_direct(q, k, v, dy, dq, dk, dv, dt == SATA_BF16, BH, n, d_k, d_v, P,
+                                                (float*)ws, s);
+    if (e != hipSuccess) return hip_fail(e, "backward (pair by pair) launch");
+    return ok();
+  }
   sata::DevTable t;
   if ((st = get_table(d_k, P, s, &t)) != SATA_OK) return st;
   void* ws = nullptr;
