@@ -95,12 +95,18 @@ sata_status sata_feature_map(const void* x, sata_dtype xt, int64_t rows, int d, 
  * depend on it beyond float rounding.  n = 0 writes a zero S_out and no y.
  * Intermediate arithmetic is float32 or on the matrix cores with float32
  * accumulation (sata_prefill_operands tells which); the state is always float32.
- * Workspace: the tuned matrix-core kernels (bf16, P = 4, d_k = d_v in
- * {16, 32}) keep every token's float32 partial readouts (576 bytes per head
- * and token at d_k = 32, chunk 64) and serve a call only while those fit in
- * 4 GB; longer calls, and every other shape, work in segments whose partial
- * sums take at most 2 GB (512 MB on the float32 vector path), so the
- * workspace stays bounded for any n.
+ * Where a matrix-core kernel covers the shape and the sequence is short for the
+ * number of features (an estimate of the two costs decides), y is formed pair
+ * by pair, sum_t f_P(q_T.k_t / sqrt(d_k)) [v_t, 1], and S_out as one sum over
+ * the tokens, with the same results up to rounding; y is the same whether
+ * S_out is NULL or not.
+ * Workspace: none pair by pair, except at most 512 MB for the sums of parts of
+ * the sequence where heads are few.  For the scan, the tuned matrix-core
+ * kernels (bf16, P = 4, d_k = d_v in {16, 32}) keep every token's float32
+ * partial readouts (576 bytes per head and token at d_k = 32, chunk 64) and
+ * serve a call only while those fit in 4 GB; longer calls, and every other
+ * shape, work in segments whose partial sums take at most 2 GB (512 MB on the
+ * float32 vector path), so the workspace stays bounded for any n.
  * SATA_ERR_HIP if the workspace cannot be allocated; SATA_ERR_UNSUPPORTED if
  * a chunk's tiles do not fit on chip (for example d_k = 255 with chunk 64). */
 sata_status sata_prefill(const void* q, const void* k, const void* v, sata_dtype dt,
@@ -116,10 +122,10 @@ sata_status sata_prefill(const void* q, const void* k, const void* v, sata_dtype
  *   y    : [B][H_kv*G][n][d_v], dtype dt (device, written)
  *   S_out: [B][H_kv][D][d_v+1] float32 or NULL: each key/value head's state,
  *          ready for sata_decode_step_grouped.
- * G = 1 is sata_prefill.  Each member of a group runs the prefill kernels of
- * sata_prefill with the shared keys and values, so the state contraction is
- * repeated G times (the readouts differ per member).  B*H_kv*G <= 65535;
- * other rules as sata_prefill. */
+ * G = 1 is sata_prefill.  Pair by pair (see sata_prefill) all members share one
+ * launch and the state is summed once; on the scan each member runs the kernels
+ * of sata_prefill with the shared keys and values, so that the state contraction
+ * is repeated G times.  B*H_kv*G <= 65535; other rules as sata_prefill. */
 sata_status sata_prefill_grouped(const void* q, const void* k, const void* v, sata_dtype dt,
                                  int B, int H_kv, int G, int n, int d_k, int d_v, int P, int chunk,
                                  void* y, float* S_out, void* stream);
@@ -161,7 +167,9 @@ typedef enum {
  * for these arguments (host only, no GPU use; same validation as sata_prefill).
  * The state is float32 in every case; callers use this to know the accuracy
  * to expect: about 2^-8 relative per term with bfloat16 operands, 2^-16 with
- * split operands, 2^-24 with float32 ones.  bfloat16 inputs take bfloat16
+ * split operands, 2^-24 with float32 ones (pair by pair, the weights take the
+ * place of the state operands, and the scores are exact products of bfloat16
+ * inputs and float32-accurate ones of float32 inputs).  bfloat16 inputs take bfloat16
  * operands, float32 inputs split operands, where a matrix-core kernel covers
  * the shape (chunk 64 and d_k, d_v <= 64 with P >= 2; other chunks only for
  * the tuned bfloat16 P = 4, d in {16, 32} kernels); float32 arithmetic
@@ -169,8 +177,9 @@ typedef enum {
 sata_status sata_prefill_operands(sata_dtype dt, int B, int H, int n, int d_k, int d_v, int P, int chunk,
                                   sata_operands* operands);
 
-/* Number of parts of the sequence that sata_prefill runs side by side for
- * these arguments (host only, no GPU use; same validation as sata_prefill).
+/* Number of parts of the sequence that the chunked scan of sata_prefill runs
+ * side by side for these arguments, where it runs as a scan (host only, no GPU
+ * use; same validation as sata_prefill).
  * 1: the chunked scan of App. A2 runs token after token.  k > 1 (a call with
  * few heads and few features on the matrix-core path, whose sequence fits one
  * segment): a first pass forms each part's state increment, sum over its

@@ -9,6 +9,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <utility>
 #include <vector>
 
@@ -16,6 +17,7 @@
 #include "prefill_blocks.hpp"
 #include "prefill_mfma.hpp"
 #include "sata.h"
+#include "state_table.hpp"
 #include "table.hpp"
 
 namespace {
@@ -49,6 +51,13 @@ struct TableEntry {
   std::vector<uint32_t> host_gen;
 };
 
+// A state-sum work list on a device, one allocation.
+struct StateTableEntry {
+  std::vector<char> host;
+  char* ptr = nullptr;
+  sata::DevStateTable dev;
+};
+
 struct Workspace {
   void* ptr = nullptr;
   size_t bytes = 0;
@@ -56,6 +65,7 @@ struct Workspace {
 
 struct DeviceCache {
   std::map<std::pair<int, int>, TableEntry> tables;
+  std::map<std::tuple<int, int, int, int, bool>, StateTableEntry> state_tables;  // (d, P, tiles, multipliers, normalisers)
   std::map<hipStream_t, Workspace> workspaces;
   std::map<hipStream_t, Workspace> counters;  // zeroed at allocation; kernels leave them zero
 };
@@ -145,6 +155,52 @@ sata_status get_table(int d, int P, hipStream_t stream, sata::DevTable* out) {
   out->D = it->second.host.D;
   out->d = d;
   out->P = P;
+  return SATA_OK;
+}
+
+// The work list of the state sum for a plan's block shape, uploaded once per device.
+sata_status get_state_table(int d, int P, const sata::StatePlan& plan, hipStream_t stream, sata::DevStateTable* out) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceCache& dc = g_devices[dev];
+  const auto key = std::make_tuple(d, P, plan.gt, plan.it, plan.normalisers);
+  auto it = dc.state_tables.find(key);
+  if (it == dc.state_tables.end()) {
+    const sata::StateTable st = sata::make_state_table(plan, d, P);
+    StateTableEntry ent;
+    auto put = [&ent](const void* p, size_t bytes) {
+      const size_t at = ent.host.size();
+      ent.host.resize((at + bytes + 255) / 256 * 256);
+      if (bytes) std::memcpy(ent.host.data() + at, p, bytes);
+      return at;
+    };
+    const size_t o_gsym = put(st.gsym.data(), st.gsym.size() * sizeof(st.gsym[0]));
+    const size_t o_list = put(st.list.data(), st.list.size() * sizeof(st.list[0]));
+    const size_t o_ftab = put(st.ftab.data(), st.ftab.size() * sizeof(st.ftab[0]));
+    const size_t o_ztab = put(st.ztab.data(), st.ztab.size() * sizeof(st.ztab[0]));
+    if ((e = hipMalloc(&ent.ptr, ent.host.size() + 256)) != hipSuccess) return hip_fail(e, "hipMalloc(state table)");
+    e = hipMemcpyAsync(ent.ptr, ent.host.data(), ent.host.size(), hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) {
+      hipFree(ent.ptr);
+      return hip_fail(e, "uploading the state table");
+    }
+    ent.dev.gsym = (const uint64_t*)(ent.ptr + o_gsym);
+    ent.dev.list = (const sata::StateBlock*)(ent.ptr + o_list);
+    ent.dev.ftab = (const int32_t*)(ent.ptr + o_ftab);
+    ent.dev.ztab = (const int32_t*)(ent.ptr + o_ztab);
+    ent.dev.gtiles = st.gtiles;
+    ent.dev.zcols = st.zcols;
+    ent.dev.tall = st.tall;
+    ent.dev.blocks = st.blocks;
+    ent.dev.zblocks = st.zblocks;
+    ent.host.clear();
+    ent.host.shrink_to_fit();
+    it = dc.state_tables.emplace(key, std::move(ent)).first;
+  }
+  *out = it->second.dev;
   return SATA_OK;
 }
 
@@ -297,6 +353,59 @@ PrefillPath prefill_path(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, 
 // offsets into a head's tensor, float32 at d = 64).
 constexpr int64_t kMaxDirectTokens = (int64_t)1 << 22;
 
+// Whether a prefill computes its outputs pair by pair (prefill_direct.hip) and
+// its state as one sum over the tokens (prefill_state.hip) rather than by the
+// chunked scan: where an estimate of the two says that it takes a tenth less.
+// Per head-token the pairs cost c (n / 2 + 128) ps (the 128: a query's own
+// chunk), the state a share of D, and the scan a larger share of D whatever n.
+// Measured on an MI355X, ns per head-token, heads enough to fill the chip:
+//   d  P  dtype     D   pairs, n = 2048 / 8192   state    scan
+//   16 4  bf16    969        0.18 / 0.66          0.23    0.48
+//   32 4  bf16   6545        0.20 / 0.68          0.96    2.09
+//   64 4  bf16  47905        0.40 / 1.45          8.9      56
+//   24 3  bf16    325        0.19 / 0.68          0.21    0.72
+//   16 4  f32     969        0.46 / 1.67          0.61    1.77
+//   32 4  f32    6545        0.80 / 2.11          2.3    11.0
+//   64 4  f32   47905        1.06 / 3.78          26      141
+// The scan has a workgroup per head and slice of features and slows down with
+// fewer of them than compute units; the other way has one per 64 to 192
+// queries.  The state counts even where the caller does not want it, so that
+// y is the same with and without.
+bool direct_pays(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int chunk, int64_t D) {
+  if (d_k > 64 || d_v > 64 || P < 2 || D > ((int64_t)1 << 22) || n > kMaxDirectTokens) return false;
+  const bool bf16 = dt == SATA_BF16;
+  const double Dd = (double)D, nct = (d_v + 16) / 16;
+  const double terms = std::max(0, P - 4);
+  double pair, state, scan;
+  if (bf16) {
+    pair = std::max(0.155, 0.075 + 0.033 * nct + (d_k > 32 ? 0.08 : 0.0)) + 0.03 * terms;
+    state = 0.12 + (d_v > 32 ? 1.9e-4 : 1.3e-4) * Dd;
+    scan = 0.35 + 0.008 * d_k + 0.65e-3 * std::min(Dd, 500.0) + 1.05e-3 * std::max(0.0, Dd - 500.0);
+  } else {
+    pair = (d_k > 32 ? 0.9 + 0.17 * nct : d_k > 16 ? 0.45 + 0.12 * nct : 0.3 + 0.1 * nct) + 0.05 * terms;
+    state = 0.15 + (d_v > 32 ? 5.4e-4 : 3.2e-4) * Dd;
+    scan = 0.5 + 0.01 * d_k + 0.4e-3 * std::min(Dd, 500.0) + 1.6e-3 * std::max(0.0, Dd - 500.0);
+  }
+  // the scan's workgroups, and the rate of the tuned kernels
+  double groups = 256.0;
+  const PrefillPath path = prefill_path(dt, BH, n, d_k, d_v, P, chunk);
+  sata::FeatPrefillPlan fp;
+  if (path == PrefillPath::kMfma32) {
+    groups = 4.0 * BH;
+    scan = 2.05;
+  } else if (path == PrefillPath::kBlocks) {
+    groups = BH;
+    scan = d_k > 16 ? 2.05 : BH >= 512 ? 0.48 : 0.6;
+  } else if (path == PrefillPath::kFeat &&
+             sata::plan_prefill_feat(D, BH, n, d_k, d_v, P, chunk, !bf16, kMaxFeatWorkspace, &fp)) {
+    groups = (double)fp.nslices * BH * fp.parts;
+  } else {
+    return false;  // float32 arithmetic
+  }
+  scan *= std::max(1.0, 256.0 / groups);
+  return 1.1 * (1e-3 * pair * (0.5 * n + 128.0) + state) <= scan;
+}
+
 // Whether the gradients are computed pair by pair (backward_direct.hip) rather
 // than by the scans over the states: c (n / 2 + 256) ps per head-token against
 // a share of the state.  Measured, ns per head-token at n = 4096 against the
@@ -309,6 +418,37 @@ bool backward_direct_pays(sata_dtype dt, int n, int d_k, int d_v, int P, int64_t
                       0.3 * std::max(0, P - 4);
   const double scan = 1.5 + 0.26 * d_k + 0.9e-3 * (double)D * (d_v + 1);
   return 1.1 * 1e-3 * pair * (0.5 * n + 256.0) <= scan;
+}
+
+// A prefill computed pair by pair: outputs for BH * G query heads, then the
+// state of each of the BH key/value heads as one sum over the tokens.
+sata_status prefill_direct(const void* q, const void* k, const void* v, sata_dtype dt, int BH, int G, int n, int d_k,
+                           int d_v, int P, void* y, float* S_out, hipStream_t s, int64_t D) {
+  sata_status st;
+  hipError_t e;
+  sata::DevTable t;
+  if ((st = get_table(d_k, P, s, &t)) != SATA_OK) return st;
+  const bool bf16 = dt == SATA_BF16;
+  sata::StatePlan plan;
+  sata::DevStateTable dst;
+  float* partial = nullptr;
+  if (S_out) {
+    plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, 0);
+    if ((st = get_state_table(d_k, P, plan, s, &dst)) != SATA_OK) return st;
+    plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, (dst.blocks + dst.zblocks) / 4);
+    if (plan.parts > 1) {
+      void* ws = nullptr;
+      if ((st = get_workspace(plan.partial_bytes, s, &ws)) != SATA_OK) return st;
+      partial = (float*)ws;
+    }
+  }
+  e = sata::launch_prefill_direct(q, k, v, y, bf16, BH * G, G, n, d_k, d_v, P, s);
+  if (e != hipSuccess) return hip_fail(e, "prefill (pair by pair) launch");
+  if (S_out) {
+    e = sata::launch_prefill_state(k, v, bf16, BH, n, d_k, d_v, P, t, dst, plan, S_out, partial, s);
+    if (e != hipSuccess) return hip_fail(e, "prefill (state) launch");
+  }
+  return ok();
 }
 
 // One prefill over BH key/value heads; q and y hold qg query heads per
@@ -502,6 +642,8 @@ sata_status sata_prefill(const void* q, const void* k, const void* v, sata_dtype
   sata_status st = check_prefill_args(dt, B, H, n, d_k, d_v, P, chunk, &D);
   if (st != SATA_OK) return st;
   if (n > 0 && (!q || !k || !v || !y)) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
+  if (n > 0 && direct_pays(dt, B * H, n, d_k, d_v, P, chunk, D))
+    return prefill_direct(q, k, v, dt, B * H, 1, n, d_k, d_v, P, y, S_out, (hipStream_t)stream, D);
   return prefill_dispatch(q, k, v, dt, B * H, n, d_k, d_v, P, chunk, y, S_out, (hipStream_t)stream, D, 1);
 }
 
@@ -515,6 +657,8 @@ sata_status sata_prefill_grouped(const void* q, const void* k, const void* v, sa
   sata_status st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D);
   if (st != SATA_OK) return st;
   if (n > 0 && (!q || !k || !v || !y)) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
+  if (n > 0 && direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D))
+    return prefill_direct(q, k, v, dt, B * H_kv, G, n, d_k, d_v, P, y, S_out, (hipStream_t)stream, D);
   const size_t esz = dt == SATA_BF16 ? 2 : 4;
   // query head g + G h of each batch row is member g of key/value head h's
   // group: with the heads of the call numbered by key/value head, member g's
@@ -680,6 +824,7 @@ void sata_release(void) {
       hipFree(t.second.weight);
       hipFree(t.second.gen);
     }
+    for (auto& t : kv.second.state_tables) hipFree(t.second.ptr);
     for (auto& w : kv.second.workspaces) hipFree(w.second.ptr);
     for (auto& w : kv.second.counters) hipFree(w.second.ptr);
   }

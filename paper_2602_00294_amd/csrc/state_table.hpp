@@ -1,0 +1,131 @@
+// Host-side work list of the state sum S = sum_t phi(k_t) (x) [v_t, 1]
+// (prefill_state.hip).
+//
+// Degree padding.  Over the d coordinates and a symbol d whose value is 1,
+// every monomial of degree 0..P-1 is a sorted tuple of exactly m = P - 1
+// symbols.  A feature is split as (i1, g): its smallest symbol i1 and the
+// remaining (m - 1)-tuple g, all of whose symbols are >= i1.  With the tuples g
+// ordered by their smallest symbol, largest first, those that go with one i1
+// are a prefix of the list, so tiles of 16 consecutive g times one i1 cover
+// the features with little padding.  At m = 1 the tuples g are the symbols
+// themselves and the only multiplier is the symbol d.
+//
+// A block is `tiles` <= gt consecutive g tiles times the `rows` <= it
+// multipliers from i0 on (the tiles that go with i0 are those that go with any
+// of them).  ftab[tab + (t * it + i) * 16 + row] is the feature of multiplier
+// i0 + i and tuple `row` of tile g0 + t (-1: none).  Blocks of more than it / 2
+// rows come first, in workgroups of their own, then the others, each fullest
+// first, so that the waves of a workgroup have like amounts of work.
+// A normaliser block is zt g tiles (zt divides gt) whose features' normalisers
+// sum_t phi_g(k_t) k_t[i1] come from one contraction with the keys:
+// ztab[row of g][i1] is the feature.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+#include <vector>
+
+#include "table.hpp"
+
+namespace sata {
+
+struct StateBlock {
+  int32_t g0, i0;
+  int32_t rows, tiles;
+  int32_t tab;
+};
+
+struct StateTable {
+  int gtiles = 0;                  // tiles of 16 tuples g, padded to whole blocks
+  int zcols = 0;                   // multipliers d + 1 rounded up to 16
+  int tall = 0, blocks = 0, zblocks = 0;  // padded to whole workgroups; blocks counts the tall ones too
+  std::vector<uint64_t> gsym;      // [gtiles * 16] symbols of g, one a byte (unused: d)
+  std::vector<StateBlock> list;    // the blocks, then the normaliser blocks
+  std::vector<int32_t> ftab;
+  std::vector<int32_t> ztab;       // [gtiles * 16][zcols]
+};
+
+// Position of the sorted tuple t[0..m) over symbols 0..d (the trailing ones
+// equal to d left out) in the library's feature order.
+inline int64_t feature_rank(int d, const int* t, int m) {
+  int p = m;
+  while (p > 0 && t[p - 1] == d) --p;
+  int64_t r = 0;
+  for (int e = 0; e < p; ++e) r += binom((int64_t)d + e - 1, e);  // lower degrees
+  int lo = 0;
+  for (int j = 0; j < p; ++j) {
+    // tuples that agree before j and have a smaller symbol x at j: the rest
+    // runs over x..d-1
+    for (int x = lo; x < t[j]; ++x) r += binom((int64_t)(d - x) + (p - j - 1) - 1, p - j - 1);
+    lo = t[j];
+  }
+  return r;
+}
+
+inline StateTable build_state_table(int d, int P, int gt, int it, int zt, bool normalisers, int waves) {
+  StateTable st;
+  const int m = P - 1, mg = m > 1 ? m - 1 : 1;
+  std::vector<std::vector<uint8_t>> gs;
+  for_each_tuple(d + 1, mg, [&](const int* t) { gs.emplace_back(t, t + mg); });
+  // stable: tuples with one smallest symbol stay in lexicographic order
+  std::stable_sort(gs.begin(), gs.end(),
+                   [](const std::vector<uint8_t>& a, const std::vector<uint8_t>& b) { return a[0] > b[0]; });
+  const int ng = (int)gs.size();
+  st.gtiles = ((ng + 15) / 16 + gt - 1) / gt * gt;  // whole blocks: kernels read them unchecked
+  st.zcols = (d + 1 + 15) / 16 * 16;
+  st.gsym.assign((size_t)st.gtiles * 16, 0);
+  for (int i = 0; i < st.gtiles * 16; ++i) {
+    uint64_t w = 0;
+    for (int j = 0; j < 8; ++j)
+      w |= (uint64_t)(uint8_t)(i < ng && j < mg ? gs[(size_t)i][(size_t)j] : d) << (8 * j);
+    st.gsym[(size_t)i] = w;
+  }
+  auto feature = [&](int g, int i1) -> int32_t {
+    if (g >= ng) return -1;
+    if (m == 1) {  // the tuples g are the features
+      const int t[1] = {gs[(size_t)g][0]};
+      return i1 == d ? (int32_t)feature_rank(d, t, 1) : -1;
+    }
+    if (i1 > gs[(size_t)g][0]) return -1;
+    int t[kMaxP];
+    t[0] = i1;
+    for (int j = 0; j < mg; ++j) t[j + 1] = gs[(size_t)g][(size_t)j];
+    return (int32_t)feature_rank(d, t, m);
+  };
+  std::vector<StateBlock> low;
+  for (int g0 = 0; g0 < st.gtiles; g0 += gt) {
+    const int top = m == 1 ? d : (int)gs[(size_t)g0 * 16][0];  // the largest multiplier of these tiles
+    for (int i0 = m == 1 ? d : 0; i0 <= top; i0 += it) {
+      StateBlock b{g0, i0, std::min(it, top + 1 - i0), 0, (int32_t)st.ftab.size()};
+      for (int t = 0; t < gt; ++t)
+        for (int i = 0; i < it; ++i)
+          for (int r = 0; r < 16; ++r) {
+            const int32_t f = i0 + i <= top ? feature((g0 + t) * 16 + r, i0 + i) : -1;
+            st.ftab.push_back(f);
+            if (f >= 0) b.tiles = t + 1;
+          }
+      (2 * b.rows > it ? st.list : low).push_back(b);
+    }
+  }
+  auto order = [&](std::vector<StateBlock>& v) {
+    std::stable_sort(v.begin(), v.end(), [](const StateBlock& x, const StateBlock& y) { return x.tiles > y.tiles; });
+    while (v.size() % (size_t)waves) v.push_back({-1, 0, 0, 0, 0});
+  };
+  order(st.list);
+  st.tall = (int)st.list.size();
+  order(low);
+  st.list.insert(st.list.end(), low.begin(), low.end());
+  st.blocks = (int)st.list.size();
+  if (normalisers) {
+    for (int g0 = 0; g0 < st.gtiles; g0 += zt) st.list.push_back({g0, 0, 0, zt, 0});
+    while (st.list.size() % (size_t)waves) st.list.push_back({-1, 0, 0, 0, 0});
+    st.ztab.resize((size_t)st.gtiles * 16 * st.zcols);
+    for (int g = 0; g < st.gtiles * 16; ++g)
+      for (int i = 0; i < st.zcols; ++i)
+        st.ztab[(size_t)g * st.zcols + i] = i <= d ? feature(g, i) : -1;
+  }
+  st.zblocks = (int)st.list.size() - st.blocks;
+  return st;
+}
+
+}  // namespace sata

@@ -1,0 +1,141 @@
+"""GPU parity of the prefill computed pair by pair (prefill_direct_kernel.hpp)
+and of the state summed over the tokens (prefill_state.hip) at the edges of
+their tiles, against the float64 oracle, with the bounds of the arithmetic that
+the library reports for the call; and of the scan kernels at the lengths that
+they still serve."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import sata_synth as syn
+from gpu_util import check_prefill_head, check_rows, check_state, operands, to_dev, to_host, y_tol
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sata():
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    import paper_2602_00294_amd as m
+    m.load_library()
+    return m
+
+
+def _half(x, dtype):
+    x = (x * np.float32(np.sqrt(0.5))).astype(np.float32)
+    return syn.round_to_bf16(x) if dtype == "bf16" else x
+
+
+def _inputs(workload, B, H, n, dk, dv, dtype):
+    q, k, v = syn.make_qkv(workload, B, H, n, dk, dv, dtype)
+    return _half(q, dtype), _half(k, dtype), v
+
+
+# d_k across the contraction steps (16, 32, 64) and their packing, d_v across
+# the column tiles with and without normaliser blocks, lengths around a chunk,
+# every number of symbols per tuple
+SHAPES = [(1, 8, 8, 4), (63, 16, 16, 3), (64, 17, 15, 4), (65, 32, 31, 4), (130, 33, 32, 3), (193, 64, 64, 3),
+          (100, 1, 1, 5), (128, 2, 48, 6), (90, 3, 63, 7), (70, 4, 2, 8), (257, 16, 33, 2), (300, 40, 16, 3),
+          (200, 31, 49, 2), (150, 8, 16, 6)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,dk,dv,P", SHAPES)
+def test_pairwise_prefill_matches_oracle(sata, n, dk, dv, P, dtype):
+    print(f"pairwise prefill n={n} dk={dk} dv={dv} P={P} {dtype}", file=sys.stderr, flush=True)
+    B, H = 1, 3
+    q, k, v = _inputs(500 + n, B, H, n, dk, dv, dtype)
+    y, S = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P)
+    torch.cuda.synchronize()
+    ops = operands(sata, dtype, B, H, n, dk, dv, P, 64)
+    for h in range(H):
+        check_prefill_head(to_host(y)[0, h], to_host(S)[0, h], q[0, h], k[0, h], v[0, h], P, ops, dtype, 64, f"h{h}")
+
+
+@pytest.mark.parametrize("B,H,n,d,P,dtype", [
+    (4, 40, 700, 32, 4, "bf16"),   # three query tiles per wave
+    (3, 43, 600, 64, 3, "bf16"),   # two
+    (4, 40, 500, 16, 4, "f32"),    # two, packed operands
+    (2, 5, 2100, 8, 4, "bf16"),    # the state in parts
+    (1, 2, 1500, 24, 3, "f32"),
+])
+def test_pairwise_prefill_many_blocks(sata, B, H, n, d, P, dtype):
+    """Blocks of several tiles per wave and sequences in parts; sampled heads."""
+    print(f"pairwise prefill B={B} H={H} n={n} d={d} P={P} {dtype}", file=sys.stderr, flush=True)
+    q, k, v = _inputs(520 + d, B, H, n, d, d, dtype)
+    y, S = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P)
+    y2, S2 = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P)
+    y3, _ = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P, want_state=False)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2) and torch.equal(S, S2) and torch.equal(y, y3)
+    ops = operands(sata, dtype, B, H, n, d, d, P, 64)
+    for b, h in {(0, 0), (B // 2, H // 2), (B - 1, H - 1)}:
+        check_prefill_head(to_host(y[b, h]), to_host(S[b, h]), q[b, h], k[b, h], v[b, h], P, ops, dtype, 64,
+                           f"b{b} h{h}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pairwise_prefill_unaligned_rows(sata, dtype):
+    """Bases that are not 16-byte aligned are read element by element, and y is
+    written element by element."""
+    n, dk, dv, P = 140, 16, 16, 4
+    print(f"pairwise prefill, unaligned rows {dtype}", file=sys.stderr, flush=True)
+    arrays = _inputs(540, 1, 1, n, dk, dv, dtype)
+    dev = []
+    for a in arrays + (np.zeros((1, 1, n, dv), np.float32),):
+        t = to_dev(a, dtype)
+        buf = torch.empty(a.size + 1, device="cuda", dtype=t.dtype)
+        buf[1:] = t.reshape(-1)
+        dev.append(buf[1:].view(*a.shape))
+    y, S = sata.prefill(*dev[:3], P, y=dev[3])
+    torch.cuda.synchronize()
+    ops = operands(sata, dtype, 1, 1, n, dk, dv, P, 64)
+    check_prefill_head(to_host(y)[0, 0], to_host(S)[0, 0], *(a[0, 0] for a in arrays), P, ops, dtype, 64, "unaligned")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pairwise_prefill_keeps_nonfinite_tokens_to_later_chunks(sata, dtype):
+    """A NaN key leaves the rows of earlier 64-token chunks as they are; a NaN
+    query leaves every other row."""
+    n, d, P = 300, 16, 4
+    print(f"pairwise prefill, non-finite tokens {dtype}", file=sys.stderr, flush=True)
+    q, k, v = (to_dev(a, dtype) for a in _inputs(550, 1, 1, n, d, d, dtype))
+    y0, _ = sata.prefill(q, k, v, P)
+    bad_k, bad_q = k.clone(), q.clone()
+    bad_k[0, 0, 150, 3] = float("nan")
+    bad_q[0, 0, 150, 3] = float("nan")
+    yk, _ = sata.prefill(q, bad_k, v, P)
+    yq, _ = sata.prefill(bad_q, k, v, P)
+    torch.cuda.synchronize()
+    assert torch.equal(yk[0, 0, :128], y0[0, 0, :128]) and torch.isnan(yk[0, 0, 150:]).all()
+    keep = [t for t in range(n) if t != 150]
+    assert torch.equal(yq[0, 0, keep], y0[0, 0, keep]) and torch.isnan(yq[0, 0, 150]).all()
+
+
+@pytest.mark.parametrize("B,H,n,d,P,dtype", [
+    (16, 32, 2400, 16, 4, "bf16"),   # the per-block matrix-core kernel
+    (2, 32, 11000, 32, 4, "bf16"),   # the d = 32 matrix-core kernel
+    (8, 32, 2100, 8, 3, "f32"),      # the generated-feature kernel, split operands
+    (8, 32, 4000, 8, 2, "bf16"),     # and with bfloat16 operands
+])
+def test_scan_prefill_of_long_sequences(sata, B, H, n, d, P, dtype):
+    """Sequences long enough for the chunked scan: sampled rows of two heads and
+    their whole states."""
+    print(f"scan prefill B={B} H={H} n={n} d={d} P={P} {dtype}", file=sys.stderr, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k, v = ((torch.randn(B, H, n, d, generator=g, device="cuda") * s).to(dt) for s in (0.5 ** 0.5, 0.5 ** 0.5, 1.0))
+    y, S = sata.prefill(q, k, v, P)
+    torch.cuda.synchronize()
+    ops = operands(sata, dtype, B, H, n, d, d, P, 64)
+    rows = sorted({0, 1, 63, 64, n // 2, n - 65, n - 2, n - 1})
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        qh, kh, vh = (t[b, h].float().cpu().numpy() for t in (q, k, v))
+        ref, _, kap = oracle.taylor_attention_rows(qh, kh, vh, P, rows)
+        check_rows(to_host(y[b, h])[rows], ref, kap, y_tol(ops, dtype), P, f"b{b} h{h}")
+        check_state(to_host(S[b, h]), kh, vh, P, ops, n, 64, f"state b{b} h{h}")

@@ -1,0 +1,93 @@
+"""The work list of the state sum (state_table.hpp), built by its own host code:
+every feature is held by exactly one (block, multiplier, tuple) slot and by
+exactly one normaliser slot, the slot's symbols are the feature's indices, and
+blocks are dealt to workgroups as the kernel assumes."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2602_00294_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <set>
+#include "state_table.hpp"
+using namespace sata;
+int main() {
+  int bad = 0;
+  for (int d : {1, 2, 3, 8, 16, 17, 24, 33, 64})
+    for (int P = 2; P <= 8; ++P) {
+      const int64_t D = feature_count(d, P);
+      if (D > 50000) continue;
+      const FeatureTable F = build_table(d, P);
+      for (int64_t f = 0; f < D; f += 1 + D / 97) {  // feature_rank against the table's order
+        int t[kMaxP];
+        const int p = packed_degree(F.packed[f]);
+        for (int j = 0; j < P - 1; ++j) t[j] = j < p ? packed_index(F.packed[f], j) : d;
+        bad += feature_rank(d, t, P - 1) != f;
+      }
+      for (int gt : {2, 4, 8})
+        for (int it : {2, 4})
+          for (int zt : {2, 4}) {
+            if (zt > gt) continue;
+            const StateTable t = build_state_table(d, P, gt, it, zt, true, 4);
+            std::vector<int> seen(D, 0), zseen(D, 0);
+            bad += t.tall % 4 || t.blocks % 4 || t.zblocks % 4 || (int)t.list.size() != t.blocks + t.zblocks;
+            bad += t.gtiles % gt || (int)t.gsym.size() != 16 * t.gtiles;
+            auto symbols = [&](int g, int i1) {
+              std::multiset<int> s;
+              for (int j = 0; j < (P > 2 ? P - 2 : 1); ++j) s.insert((int)(t.gsym[g] >> (8 * j) & 255));
+              s.insert(i1);
+              s.erase(d);
+              return s;
+            };
+            auto indices = [&](int f) {
+              std::multiset<int> s;
+              for (int j = 0; j < packed_degree(F.packed[f]); ++j) s.insert(packed_index(F.packed[f], j));
+              return s;
+            };
+            for (int b = 0; b < t.blocks; ++b) {
+              const StateBlock& B = t.list[b];
+              if (B.g0 < 0) continue;
+              bad += B.g0 + gt > t.gtiles || B.i0 + B.rows > d + 1 || (b < t.tall) != (2 * B.rows > it);
+              for (int x = 0; x < gt; ++x)
+                for (int i = 0; i < it; ++i)
+                  for (int r = 0; r < 16; ++r) {
+                    const int f = t.ftab[B.tab + (x * it + i) * 16 + r];
+                    if (f < 0) continue;
+                    ++seen[f];
+                    bad += x >= B.tiles || i >= B.rows || symbols((B.g0 + x) * 16 + r, B.i0 + i) != indices(f);
+                  }
+            }
+            std::set<int> tiles;
+            for (int b = t.blocks; b < (int)t.list.size(); ++b)
+              if (t.list[b].g0 >= 0)
+                for (int x = 0; x < zt; ++x) bad += !tiles.insert(t.list[b].g0 + x).second;
+            bad += (int)tiles.size() != t.gtiles || *tiles.rbegin() != t.gtiles - 1;
+            for (int g = 0; g < 16 * t.gtiles; ++g)
+              for (int i = 0; i < t.zcols; ++i) {
+                const int f = t.ztab[(size_t)g * t.zcols + i];
+                if (f < 0) continue;
+                ++zseen[f];
+                bad += i > d || symbols(g, i) != indices(f);
+              }
+            for (int64_t f = 0; f < D; ++f) bad += seen[f] != 1 || zseen[f] != 1;
+          }
+    }
+  std::printf("%d\n", bad);
+  return bad != 0;
+}
+"""
+
+
+def test_state_table_holds_every_feature_once(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(PROGRAM)
+    subprocess.run([gxx, "-O1", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)], check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
