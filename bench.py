@@ -870,8 +870,8 @@ def main():
     pre_ach = pre_flops / (pre_ms * 1e-3) / 1e12
     dec_bytes = decode_bytes_per_head_step(DK, DV, P, 2) * B * H
     dec_ach = dec_bytes / (dec_ms * 1e-3 / args.decode_steps) / 1e9
-    t_main, t_fin = measured_traffic("prefill_mfma_main"), measured_traffic("prefill_mfma_finalize")
-    pre_traffic = t_main + t_fin if t_main is not None and t_fin is not None else None
+    t_y, t_state = measured_traffic("prefill_direct_kernel"), measured_traffic("prefill_state_kernel")
+    pre_traffic = t_y + t_state if t_y is not None and t_state is not None else None
     roof_pre = {"kernel": "sata_prefill (all launches of one call)", "bound": "mfma",
                 "achieved": pre_ach, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": pre_ach / PEAK_BF16_TFLOPS, "traffic": pre_traffic,
