@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "state_table.hpp"
+
 namespace sata {
 
 // Zero entries (degree 0, weight 0) that follow the D features of a device
@@ -140,27 +142,25 @@ hipError_t launch_prefill_direct(const void* q, const void* k, const void* v, vo
                                  int n, int dk, int dv, int P, hipStream_t s);
 
 // ---- state after a sequence (prefill_state.hip) --------------------------------
-struct StateTable;  // state_table.hpp
-// A StateTable on a device.
+// A StateTable (state_table.hpp) on a device.
 struct DevStateTable {
   const uint64_t* gsym = nullptr;
-  const struct StateBlock* list = nullptr;
+  const StateBlock* list = nullptr;
   const int32_t* ftab = nullptr;
   const int32_t* ztab = nullptr;
-  int gtiles = 0, zcols = 0, tall = 0, blocks = 0, zblocks = 0;
+  int zcols = 0, tall = 0, blocks = 0, zblocks = 0;
 };
 struct StatePlan {
-  int nct = 0;               // column tiles
-  int gt = 0, it = 0;        // tuple tiles and multipliers per block
-  bool split = false;        // split operands (float32 inputs)
-  bool normalisers = false;  // normalisers from blocks of their own
-  int parts = 1;             // parts of the sequence summed side by side
+  int nct = 0;       // column tiles
+  StateShape shape;  // the work list's block shape
+  int parts = 1;     // parts of the sequence summed side by side
   int part_len = 0;          // tokens per part
   size_t partial_bytes = 0;  // the parts' states, when parts > 1
 };
 // nwg: workgroups per head of the table (0 before it is known: one part).
 StatePlan plan_prefill_state(int64_t D, int BH, int n, int dv, bool bf16, int nwg);
-StateTable make_state_table(const StatePlan& p, int dk, int P);
+// The work list of (d_k, P) as the kernel deals it to workgroups.
+StateTable make_state_table(int dk, int P, const StateShape& shape);
 // S_out [BH][D][d_v+1] = the state after n >= 1 tokens; d_k, d_v <= 64, P >= 2.
 hipError_t launch_prefill_state(const void* k, const void* v, bool bf16, int BH, int n, int dk, int dv, int P,
                                 const DevTable& t, const DevStateTable& st, const StatePlan& plan, float* S_out,

@@ -56,14 +56,6 @@ __device__ __forceinline__ void load8(const float* p, float (&x)[8]) {
   x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w, x[4] = b.x, x[5] = b.y, x[6] = b.z, x[7] = b.w;
 }
 
-// g tiles and multipliers per block: GT * IT * NCT accumulator tiles (4
-// registers each) beside the operands at two waves per SIMD.
-constexpr int gt_for(int nct, bool x3) { return x3 ? (nct <= 2 ? 4 : 2) : (nct == 1 ? 8 : 4); }
-constexpr int it_for(int nct, bool x3) { return x3 ? (nct == 1 ? 4 : 2) : (nct <= 2 ? 4 : 2); }
-
-// g tiles of a normaliser block (up to 5 accumulator tiles each).
-constexpr int zt_for(bool x3) { return x3 ? 2 : 4; }
-
 // bf16 per LDS row of [V | 1]: an odd multiple of 8 banks, so that the rows a
 // half wave reads transposed lie in distinct banks.
 __host__ __device__ constexpr int v_row(int nct) { return 16 * (nct | 1); }
@@ -91,7 +83,7 @@ struct StateArgs {
 template <typename T, bool X3, int NCT, int MG>
 __global__ void __launch_bounds__(kNW * 64, 2) prefill_state_kernel(const T* __restrict__ k_, const T* __restrict__ v_,
                                                                     StateArgs a) {
-  constexpr int GT = gt_for(NCT, X3), IT = it_for(NCT, X3);
+  constexpr int GT = state_gt(NCT, X3), IT = state_it(NCT, X3);
   constexpr int PL = X3 ? 2 : 1;
   constexpr int kEV = 16 / sizeof(T);
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -302,7 +294,7 @@ __global__ void __launch_bounds__(kNW * 64, 2) prefill_state_kernel(const T* __r
 
   // ---- a normaliser block: phi_g of its tiles times KT tiles of the keys
   auto normaliser_block = [&](auto ktc) {
-    constexpr int KT = decltype(ktc)::value, ZT = zt_for(X3);
+    constexpr int KT = decltype(ktc)::value, ZT = state_zt(X3);
     static_assert(ZT <= GT, "symbols of a normaliser block's tiles");
     f32x4 acc[ZT][KT];
 #pragma unroll
@@ -549,17 +541,12 @@ hipError_t launch_nct(int nct, const void* k, const void* v, const StateArgs& a,
 
 }  // namespace
 
-StateTable make_state_table(const StatePlan& p, int dk, int P) {
-  return build_state_table(dk, P, p.gt, p.it, zt_for(p.split), p.normalisers, kNW);
-}
+StateTable make_state_table(int dk, int P, const StateShape& shape) { return build_state_table(dk, P, shape, kNW); }
 
 StatePlan plan_prefill_state(int64_t D, int BH, int n, int dv, bool bf16, int nwg) {
   StatePlan p;
-  p.split = !bf16;
-  p.normalisers = dv % 16 == 0;
   p.nct = (dv + 15) / 16;
-  p.gt = gt_for(p.nct, p.split);
-  p.it = it_for(p.nct, p.split);
+  p.shape = state_shape(dv, !bf16);
   p.parts = 1;
   p.part_len = std::max(kCh, (n + kCh - 1) / kCh * kCh);
   // Two workgroups fit a compute unit.  Below four rounds of them the tokens
@@ -599,7 +586,7 @@ hipError_t launch_prefill_state(const void* k, const void* v, bool bf16, int BH,
   a.zcols = st.zcols;
   a.mg = P > 2 ? P - 2 : 1;
   a.by_xcd = BH >= 8;
-  a.ones = !plan.normalisers;
+  a.ones = !plan.shape.normalisers;
   hipError_t e = bf16 ? launch_nct<u16, false>(plan.nct, k, v, a, plan.parts, s)
                       : launch_nct<float, true>(plan.nct, k, v, a, plan.parts, s);
   if (e != hipSuccess || plan.parts == 1) return e;

@@ -65,7 +65,7 @@ struct Workspace {
 
 struct DeviceCache {
   std::map<std::pair<int, int>, TableEntry> tables;
-  std::map<std::tuple<int, int, int, int, bool>, StateTableEntry> state_tables;  // (d, P, tiles, multipliers, normalisers)
+  std::map<std::tuple<int, int, sata::StateShape>, StateTableEntry> state_tables;  // (d, P, shape)
   std::map<hipStream_t, Workspace> workspaces;
   std::map<hipStream_t, Workspace> counters;  // zeroed at allocation; kernels leave them zero
 };
@@ -158,17 +158,18 @@ sata_status get_table(int d, int P, hipStream_t stream, sata::DevTable* out) {
   return SATA_OK;
 }
 
-// The work list of the state sum for a plan's block shape, uploaded once per device.
-sata_status get_state_table(int d, int P, const sata::StatePlan& plan, hipStream_t stream, sata::DevStateTable* out) {
+// The work list of the state sum for a block shape, uploaded once per device.
+sata_status get_state_table(int d, int P, const sata::StateShape& shape, hipStream_t stream,
+                            sata::DevStateTable* out) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   std::lock_guard<std::mutex> lock(g_mu);
   DeviceCache& dc = g_devices[dev];
-  const auto key = std::make_tuple(d, P, plan.gt, plan.it, plan.normalisers);
+  const auto key = std::make_tuple(d, P, shape);
   auto it = dc.state_tables.find(key);
   if (it == dc.state_tables.end()) {
-    const sata::StateTable st = sata::make_state_table(plan, d, P);
+    const sata::StateTable st = sata::make_state_table(d, P, shape);
     StateTableEntry ent;
     auto put = [&ent](const void* p, size_t bytes) {
       const size_t at = ent.host.size();
@@ -191,7 +192,6 @@ sata_status get_state_table(int d, int P, const sata::StatePlan& plan, hipStream
     ent.dev.list = (const sata::StateBlock*)(ent.ptr + o_list);
     ent.dev.ftab = (const int32_t*)(ent.ptr + o_ftab);
     ent.dev.ztab = (const int32_t*)(ent.ptr + o_ztab);
-    ent.dev.gtiles = st.gtiles;
     ent.dev.zcols = st.zcols;
     ent.dev.tall = st.tall;
     ent.dev.blocks = st.blocks;
@@ -434,7 +434,7 @@ sata_status prefill_direct(const void* q, const void* k, const void* v, sata_dty
   float* partial = nullptr;
   if (S_out) {
     plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, 0);
-    if ((st = get_state_table(d_k, P, plan, s, &dst)) != SATA_OK) return st;
+    if ((st = get_state_table(d_k, P, plan.shape, s, &dst)) != SATA_OK) return st;
     plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, (dst.blocks + dst.zblocks) / 4);
     if (plan.parts > 1) {
       void* ws = nullptr;

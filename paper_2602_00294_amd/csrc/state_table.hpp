@@ -23,11 +23,41 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <tuple>
 #include <vector>
 
 #include "table.hpp"
 
 namespace sata {
+
+// Block shape of a work list: all that the list depends on besides (d, P), so
+// (d, P, shape) names a list, and the shape that a kernel assumes.
+struct StateShape {
+  int gt = 0, it = 0;        // g tiles and multipliers of a feature block
+  int zt = 0;                // g tiles of a normaliser block
+  bool normalisers = false;  // normalisers from blocks of their own
+  bool operator<(const StateShape& o) const {
+    return std::tie(gt, it, zt, normalisers) < std::tie(o.gt, o.it, o.zt, o.normalisers);
+  }
+};
+
+// Feature blocks: gt * it * (column tiles) accumulator tiles (4 registers each)
+// beside the operands at two waves per SIMD; normaliser blocks: up to 5
+// accumulator tiles per g tile.  split: split operands (float32 inputs).
+constexpr int state_gt(int col_tiles, bool split) { return split ? (col_tiles <= 2 ? 4 : 2) : (col_tiles == 1 ? 8 : 4); }
+constexpr int state_it(int col_tiles, bool split) { return split ? (col_tiles == 1 ? 4 : 2) : (col_tiles <= 2 ? 4 : 2); }
+constexpr int state_zt(bool split) { return split ? 2 : 4; }
+
+// The shape for values of d_v columns.
+inline StateShape state_shape(int dv, bool split) {
+  const int nct = (dv + 15) / 16;
+  StateShape s;
+  s.gt = state_gt(nct, split);
+  s.it = state_it(nct, split);
+  s.zt = state_zt(split);
+  s.normalisers = dv % 16 == 0;
+  return s;
+}
 
 struct StateBlock {
   int32_t g0, i0;
@@ -126,6 +156,10 @@ inline StateTable build_state_table(int d, int P, int gt, int it, int zt, bool n
   }
   st.zblocks = (int)st.list.size() - st.blocks;
   return st;
+}
+
+inline StateTable build_state_table(int d, int P, const StateShape& s, int waves) {
+  return build_state_table(d, P, s.gt, s.it, s.zt, s.normalisers, waves);
 }
 
 }  // namespace sata

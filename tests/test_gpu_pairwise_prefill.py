@@ -79,6 +79,25 @@ def test_pairwise_prefill_many_blocks(sata, B, H, n, d, P, dtype):
                            f"b{b} h{h}")
 
 
+@pytest.mark.parametrize("calls", [(("bf16", 32), ("f32", 16)), (("bf16", 64), ("f32", 32))])
+@pytest.mark.parametrize("reverse", [False, True])
+def test_pairwise_prefill_tables_of_both_types(sata, calls, reverse):
+    """bfloat16 and float32 calls of one (d_k, P) whose blocks of features have
+    the same shape and those of normalisers not: whichever comes first, every
+    element of the second one's state is written."""
+    n, dk, P = 100, 32, 4
+    sata.release()
+    for dtype, dv in calls[::-1] if reverse else calls:
+        print(f"pairwise prefill tables {dtype} dv={dv}", file=sys.stderr, flush=True)
+        q, k, v = _inputs(530, 1, 1, n, dk, dv, dtype)
+        S = torch.full((1, 1, oracle.feature_count(dk, P), dv + 1), float("nan"), device="cuda")
+        y, _ = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P, S=S)
+        torch.cuda.synchronize()
+        ops = operands(sata, dtype, 1, 1, n, dk, dv, P, 64)
+        check_prefill_head(to_host(y)[0, 0], to_host(S)[0, 0], q[0, 0], k[0, 0], v[0, 0], P, ops, dtype, 64,
+                           f"{dtype} dv={dv}")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_pairwise_prefill_unaligned_rows(sata, dtype):
     """Bases that are not 16-byte aligned are read element by element, and y is

@@ -81,13 +81,66 @@ int main() {
 }
 """
 
+# Every call's list comes out of one cache keyed by (d, P, shape), filled in
+# either order of bfloat16 and float32 and of d_v: it has to be the list that
+# the call's kernel walks, with its number of g tiles per normaliser block.
+CACHE_PROGRAM = r"""
+#include <cstdio>
+#include <map>
+#include "state_table.hpp"
+using namespace sata;
+int main() {
+  int bad = 0;
+  for (int d : {8, 32})
+    for (int order = 0; order < 2; ++order) {
+      const int P = 4;
+      const int64_t D = feature_count(d, P);
+      std::map<std::tuple<int, int, StateShape>, StateTable> cache;
+      for (int i = 0; i < 128; ++i) {
+        const int call = order ? 127 - i : i, dv = call / 2 + 1;
+        const bool split = call % 2;
+        const StateShape s = state_shape(dv, split);
+        bad += s.zt != state_zt(split) || s.gt != state_gt((dv + 15) / 16, split) ||
+               s.it != state_it((dv + 15) / 16, split) || s.normalisers != (dv % 16 == 0);
+        const auto key = std::make_tuple(d, P, s);
+        auto it = cache.find(key);
+        if (it == cache.end()) it = cache.emplace(key, build_state_table(d, P, s, 4)).first;
+        const StateTable& t = it->second;
+        std::vector<int> seen(D, 0);
+        for (int b = t.blocks; b < (int)t.list.size(); ++b) {
+          const StateBlock& B = t.list[b];
+          if (B.g0 < 0) continue;
+          bad += B.g0 + state_zt(split) > t.gtiles;
+          for (int x = 0; x < state_zt(split) && B.g0 + x < t.gtiles; ++x)
+            for (int r = 0; r < 16; ++r)
+              for (int z = 0; z < t.zcols; ++z) {
+                const int f = t.ztab[(size_t)((B.g0 + x) * 16 + r) * t.zcols + z];
+                if (f >= 0) ++seen[f];
+              }
+        }
+        for (int64_t f = 0; f < D; ++f) bad += seen[f] != (dv % 16 == 0);
+      }
+    }
+  std::printf("%d\n", bad);
+  return bad != 0;
+}
+"""
 
-def test_state_table_holds_every_feature_once(tmp_path):
+
+def _run(tmp_path, program):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no g++")
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.run([gxx, "-O1", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+def test_state_table_holds_every_feature_once(tmp_path):
+    _run(tmp_path, PROGRAM)
+
+
+def test_cached_state_table_is_the_calls_own(tmp_path):
+    _run(tmp_path, CACHE_PROGRAM)
