@@ -126,13 +126,15 @@ __global__ void __launch_bounds__(kNW * 64, 2) prefill_state_kernel(const T* __r
   }
 
   // ---- this lane's tuples: where the coordinate rows of their symbols start
-  // (more than two symbols a tuple: the packed symbols)
+  // (more than two symbols a tuple: the packed symbols).  A normaliser block
+  // has fewer tiles than a feature block, and the last one's end with the list.
+  const int gts = zwg ? state_zt(X3) : GT;
   constexpr int kOff = MG ? MG : 1;
   int off[GT][kOff];
   uint64_t gs[MG ? 1 : GT];
 #pragma unroll
   for (int t = 0; t < GT; ++t) {
-    const uint64_t w = live ? a.gsym[(blk.g0 + t) * 16 + l15] : 0;
+    const uint64_t w = live && t < gts ? a.gsym[(blk.g0 + t) * 16 + l15] : 0;
 #pragma unroll
     for (int j = 0; j < kOff; ++j) off[t][j] = (int)((w >> (8 * j)) & 0xff) * kRS + 8 * g4;
     if constexpr (MG == 0) gs[t] = w;
