@@ -98,8 +98,10 @@ sata_status sata_feature_map(const void* x, sata_dtype xt, int64_t rows, int d, 
  * Where a matrix-core kernel covers the shape and the sequence is short for the
  * number of features (an estimate of the two costs decides), y is formed pair
  * by pair, sum_t f_P(q_T.k_t / sqrt(d_k)) [v_t, 1], and S_out as one sum over
- * the tokens, with the same results up to rounding; y is the same whether
- * S_out is NULL or not.
+ * the tokens, with the same results up to rounding.  The state is part of the
+ * cost, so with S_out NULL more calls go pair by pair, and y then agrees with
+ * that of the call with a state up to rounding; calls alike in sizes, in
+ * S_out being NULL and in 16-byte alignment go one way.
  * Workspace: none pair by pair, except at most 512 MB for the sums of parts of
  * the sequence where heads are few.  For the scan, the tuned matrix-core
  * kernels (bf16, P = 4, d_k = d_v in {16, 32}) keep every token's float32

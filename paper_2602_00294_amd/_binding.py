@@ -201,8 +201,9 @@ def prefill_operands(dtype, B: int, H: int, n: int, d_k: int, d_v: int, P: int, 
 
 
 def prefill_parts(dtype, B: int, H: int, n: int, d_k: int, d_v: int, P: int, chunk: int = 64) -> int:
-    """Number of parts of the sequence that prefill runs side by side for these
-    arguments (host only; 1: one scan from the first token to the last)."""
+    """Number of parts of the sequence that the chunked scan of prefill runs side by
+    side for these arguments, where it runs as a scan (host only; 1: one scan from
+    the first token to the last)."""
     torch = _torch()
     code = {torch.float32: SATA_F32, torch.bfloat16: SATA_BF16}.get(dtype)
     if code is None:

@@ -106,6 +106,7 @@ struct FeatPrefillPlan {
   bool split = false;      // split operands (hi + lo bfloat16 pairs, three products per product)
   bool narrow = false;     // slices of 256 features (for few features or few heads)
   int nslices = 0;         // workgroups per head
+  int wave_features = 0;   // features of the busiest wave, in tiles of 16
   int seg_len = 0;         // tokens per segment (partial sums of one segment in the workspace)
   int parts = 1;           // parts of a one-segment call that run side by side (states summed first)
   int part_len = 0;        // tokens per part

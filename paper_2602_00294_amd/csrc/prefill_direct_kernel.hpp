@@ -50,6 +50,7 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
+#include "route.hpp"
 #include "series.hpp"
 
 namespace sata {
@@ -541,11 +542,9 @@ hipError_t launch_one(const void* q, const void* k, const void* v, void* y, int 
 template <typename T, bool X3, bool PK, int NKT, int NCT>
 hipError_t launch_nq(const void* q, const void* k, const void* v, void* y, int heads, int qg, int n, int dk, int dv,
                      int P, hipStream_t s) {
-  // Many queries per wave reuse the chunk's operands; one tile per wave where
-  // larger blocks would leave compute units without work.
-  constexpr int kWide = X3 || NCT >= 4 ? 2 : 3;
-  const int64_t wide = ((int64_t)n + kCh * kWide - 1) / (kCh * kWide) * heads;
-  if (wide >= 512) return launch_one<T, X3, PK, NKT, NCT, kWide>(q, k, v, y, heads, qg, n, dk, dv, P, s);
+  constexpr int kWide = direct_wide_tiles(X3, NCT);
+  if (direct_query_tiles(X3, dv, heads, n) == kWide)
+    return launch_one<T, X3, PK, NKT, NCT, kWide>(q, k, v, y, heads, qg, n, dk, dv, P, s);
   return launch_one<T, X3, PK, NKT, NCT, 1>(q, k, v, y, heads, qg, n, dk, dv, P, s);
 }
 

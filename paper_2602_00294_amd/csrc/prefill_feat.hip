@@ -830,6 +830,7 @@ bool plan_prefill_feat(int64_t D, int BH, int n, int dk, int dv, int P, int chun
   plan->nct = nct;
   plan->split = split;
   plan->nslices = (int)((D + fslice - 1) / fslice);
+  plan->wave_features = (int)std::min<int64_t>(fslice / kNW, (D + 15) / 16 * 16);
   plan->lds_main = (size_t)lds_for(nct, split);
   const size_t per_token = sizeof(float) * (size_t)plan->nslices * BH * E;
   int64_t seg = (int64_t)(max_ws_bytes / per_token) / kCh * kCh;

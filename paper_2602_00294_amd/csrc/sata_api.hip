@@ -16,7 +16,9 @@
 #include "kernels.hpp"
 #include "prefill_blocks.hpp"
 #include "prefill_mfma.hpp"
+#include "route.hpp"
 #include "sata.h"
+#include "sata_testing.h"
 #include "state_table.hpp"
 #include "table.hpp"
 
@@ -353,57 +355,54 @@ PrefillPath prefill_path(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, 
 // offsets into a head's tensor, float32 at d = 64).
 constexpr int64_t kMaxDirectTokens = (int64_t)1 << 22;
 
+// Whether the pair-by-pair prefill covers a shape.
+bool direct_covers(int n, int d_k, int d_v, int P, int64_t D) {
+  return d_k <= 64 && d_v <= 64 && P >= 2 && D <= ((int64_t)1 << 22) && n <= kMaxDirectTokens;
+}
+
 // Whether a prefill computes its outputs pair by pair (prefill_direct.hip) and
-// its state as one sum over the tokens (prefill_state.hip) rather than by the
-// chunked scan: where an estimate of the two says that it takes a tenth less.
-// Per head-token the pairs cost c (n / 2 + 128) ps (the 128: a query's own
-// chunk), the state a share of D, and the scan a larger share of D whatever n.
-// Measured on an MI355X, ns per head-token, heads enough to fill the chip:
-//   d  P  dtype     D   pairs, n = 2048 / 8192   state    scan
-//   16 4  bf16    969        0.18 / 0.66          0.23    0.48
-//   32 4  bf16   6545        0.20 / 0.68          0.96    2.09
-//   64 4  bf16  47905        0.40 / 1.45          8.9      56
-//   24 3  bf16    325        0.19 / 0.68          0.21    0.72
-//   16 4  f32     969        0.46 / 1.67          0.61    1.77
-//   32 4  f32    6545        0.80 / 2.11          2.3    11.0
-//   64 4  f32   47905        1.06 / 3.78          26      141
-// The scan has a workgroup per head and slice of features and slows down with
-// fewer of them than compute units; the other way has one per 64 to 192
-// queries.  The state counts even where the caller does not want it, so that
-// y is the same with and without.
-bool direct_pays(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int chunk, int64_t D) {
-  if (d_k > 64 || d_v > 64 || P < 2 || D > ((int64_t)1 << 22) || n > kMaxDirectTokens) return false;
-  const bool bf16 = dt == SATA_BF16;
-  const double Dd = (double)D, nct = (d_v + 16) / 16;
-  const double terms = std::max(0, P - 4);
-  double pair, state, scan;
-  if (bf16) {
-    pair = std::max(0.155, 0.075 + 0.033 * nct + (d_k > 32 ? 0.08 : 0.0)) + 0.03 * terms;
-    state = 0.12 + (d_v > 32 ? 1.9e-4 : 1.3e-4) * Dd;
-    scan = 0.35 + 0.008 * d_k + 0.65e-3 * std::min(Dd, 500.0) + 1.05e-3 * std::max(0.0, Dd - 500.0);
-  } else {
-    pair = (d_k > 32 ? 0.9 + 0.17 * nct : d_k > 16 ? 0.45 + 0.12 * nct : 0.3 + 0.1 * nct) + 0.05 * terms;
-    state = 0.15 + (d_v > 32 ? 5.4e-4 : 3.2e-4) * Dd;
-    scan = 0.5 + 0.01 * d_k + 0.4e-3 * std::min(Dd, 500.0) + 1.6e-3 * std::max(0.0, Dd - 500.0);
-  }
-  // the scan's workgroups, and the rate of the tuned kernels
-  double groups = 256.0;
+// its state, where it is asked for, as one sum over the tokens
+// (prefill_state.hip) rather than by the chunked scan: by the estimates of
+// route.hpp.  A grouped call asks for its key/value heads alone: each member is
+// bitwise the single-head prefill of its queries, so both take one way.
+bool direct_pays(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int chunk, int64_t D, bool want_state,
+                 bool vectors) {
+  if (!direct_covers(n, d_k, d_v, P, D)) return false;
+  sata::RouteCall r;
+  r.bf16 = dt == SATA_BF16;
+  r.dk = d_k;
+  r.dv = d_v;
+  r.P = P;
+  r.D = D;
+  r.heads = BH;
+  r.n = n;
+  r.vectors = vectors;
+  sata::ScanShape scan;
   const PrefillPath path = prefill_path(dt, BH, n, d_k, d_v, P, chunk);
   sata::FeatPrefillPlan fp;
-  if (path == PrefillPath::kMfma32) {
-    groups = 4.0 * BH;
-    scan = 2.05;
-  } else if (path == PrefillPath::kBlocks) {
-    groups = BH;
-    scan = d_k > 16 ? 2.05 : BH >= 512 ? 0.48 : 0.6;
+  if (path == PrefillPath::kMfma32 || path == PrefillPath::kBlocks) {
+    scan.tuned = true;
+    scan.chunk = chunk;
   } else if (path == PrefillPath::kFeat &&
-             sata::plan_prefill_feat(D, BH, n, d_k, d_v, P, chunk, !bf16, kMaxFeatWorkspace, &fp)) {
-    groups = (double)fp.nslices * BH * fp.parts;
+             sata::plan_prefill_feat(D, BH, n, d_k, d_v, P, chunk, !r.bf16, kMaxFeatWorkspace, &fp)) {
+    scan.wave_features = fp.wave_features;
+    scan.slices = fp.nslices;
+    scan.parts = fp.parts;
   } else {
     return false;  // float32 arithmetic
   }
-  scan *= std::max(1.0, 256.0 / groups);
-  return 1.1 * (1e-3 * pair * (0.5 * n + 128.0) + state) <= scan;
+  double t = sata::pairs_us(r);
+  if (want_state) {
+    const double wgs = sata::state_workgroups(r);
+    t = std::max(17.5, t + sata::state_us(r, wgs, sata::plan_prefill_state(D, BH, n, d_v, r.bf16, (int)(wgs + 0.5)).parts));
+  }
+  return t <= sata::scan_us(r, scan);
+}
+
+// Whether the rows of q, k and v are whole 16-byte vectors.
+bool vector_rows(const void* q, const void* k, const void* v, sata_dtype dt, int d_k, int d_v) {
+  const int elems = dt == SATA_BF16 ? 8 : 4;
+  return d_k % elems == 0 && d_v % elems == 0 && (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v) & 15) == 0;
 }
 
 // Whether the gradients are computed pair by pair (backward_direct.hip) rather
@@ -411,8 +410,9 @@ bool direct_pays(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int chun
 // a share of the state.  Measured, ns per head-token at n = 4096 against the
 // scans: d = 32, P = 4 bf16 3.4 / 206, d = 16, P = 3 bf16 3.1 / 10, d = 16,
 // P = 4 f32 6.0 / 28.5, d = 64, P = 2 f32 20 / 28.
+bool backward_direct_covers(int n, int P) { return P >= 2 && n <= kMaxDirectTokens; }
 bool backward_direct_pays(sata_dtype dt, int n, int d_k, int d_v, int P, int64_t D) {
-  if (P < 2 || n > kMaxDirectTokens) return false;
+  if (!backward_direct_covers(n, P)) return false;
   const int tiles = (std::max(d_k, d_v) + 15) / 16;
   const double pair = (dt == SATA_BF16 ? (tiles <= 2 ? 1.75 : 2.6) : (tiles == 1 ? 3.0 : tiles == 2 ? 3.7 : 10.0)) +
                       0.3 * std::max(0, P - 4);
@@ -547,6 +547,94 @@ sata_status decode_step(float* S, float* R, const void* q, const void* k, const 
   return ok();
 }
 
+// By which way a prefill or a backward is computed.
+enum class Way { kEstimate, kPairs, kScan };
+
+sata_status check_groups(int B, int H_kv, int G) {
+  if (G < 1) return fail(SATA_ERR_INVALID_ARG, "G=%d must be >= 1", G);
+  if (B >= 1 && H_kv >= 1 && (int64_t)B * H_kv * G > kMaxHeads)
+    return fail(SATA_ERR_TOO_LARGE, "B*H_kv*G=%lld exceeds %d", (long long)B * H_kv * G, kMaxHeads);
+  return SATA_OK;
+}
+
+// sata_prefill (G = 1) and sata_prefill_grouped.
+sata_status prefill(Way way, const void* q, const void* k, const void* v, sata_dtype dt, int B, int H_kv, int G, int n,
+                    int d_k, int d_v, int P, int chunk, void* y, float* S_out, void* stream) {
+  int64_t D = 0;
+  sata_status st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D);
+  if (st != SATA_OK) return st;
+  if (n > 0 && (!q || !k || !v || !y)) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
+  if (way == Way::kPairs && !direct_covers(n, d_k, d_v, P, D))
+    return fail(SATA_ERR_UNSUPPORTED, "no pair-by-pair prefill for n=%d d_k=%d d_v=%d P=%d", n, d_k, d_v, P);
+  if (n > 0 && (way == Way::kPairs ||
+                (way == Way::kEstimate && direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D, S_out != nullptr,
+                                                      vector_rows(q, k, v, dt, d_k, d_v)))))
+    return prefill_direct(q, k, v, dt, B * H_kv, G, n, d_k, d_v, P, y, S_out, (hipStream_t)stream, D);
+  const size_t esz = dt == SATA_BF16 ? 2 : 4;
+  // query head g + G h of each batch row is member g of key/value head h's
+  // group: with the heads of the call numbered by key/value head, member g's
+  // queries and outputs start g heads in and lie G heads apart
+  for (int g = 0; g < G; ++g) {
+    const void* qg = (const char*)q + esz * (size_t)g * (size_t)n * (size_t)d_k;
+    void* yg = (char*)y + esz * (size_t)g * (size_t)n * (size_t)d_v;
+    st = prefill_dispatch(qg, k, v, dt, B * H_kv, n, d_k, d_v, P, chunk, yg, g == 0 ? S_out : nullptr,
+                          (hipStream_t)stream, D, G);
+    if (st != SATA_OK) return st;
+    if (n == 0) break;
+  }
+  return ok();
+}
+
+sata_status check_backward_args(sata_dtype dt, int B, int H, int n, int d_k, int d_v, int P, int chunk, int64_t* D) {
+  if (!valid_dtype(dt)) return fail(SATA_ERR_INVALID_ARG, "unknown dtype %d", (int)dt);
+  if (B < 1 || H < 1) return fail(SATA_ERR_INVALID_ARG, "B=%d H=%d must be >= 1", B, H);
+  if (n < 0) return fail(SATA_ERR_INVALID_ARG, "n=%d < 0", n);
+  sata_status st = check_dims(d_k, d_v, P, D);
+  if (st != SATA_OK) return st;
+  if ((int64_t)B * H > kMaxHeads) return fail(SATA_ERR_TOO_LARGE, "B*H=%lld exceeds %d", (long long)B * H, kMaxHeads);
+  if (chunk != 16 && chunk != 32 && chunk != 64)
+    return fail(SATA_ERR_UNSUPPORTED, "chunk=%d; the backward supports 16, 32, 64", chunk);
+  if (d_k > sata::kMaxBackwardDim || d_v > sata::kMaxBackwardDim)
+    return fail(SATA_ERR_UNSUPPORTED, "the backward supports d_k, d_v <= %d", sata::kMaxBackwardDim);
+  return SATA_OK;
+}
+
+sata_status backward(Way way, const void* q, const void* k, const void* v, const void* dy, sata_dtype dt, int B, int H,
+                     int n, int d_k, int d_v, int P, int chunk, void* dq, void* dk, void* dv, void* stream) {
+  int64_t D = 0;
+  sata_status st = check_backward_args(dt, B, H, n, d_k, d_v, P, chunk, &D);
+  if (st != SATA_OK) return st;
+  if (n == 0) return ok();
+  if (!q || !k || !v || !dy || !dq || !dk || !dv) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
+  const int BH = B * H;
+  sata::BackwardPlan plan;
+  sata::PrefillGenericPlan fwd;
+  if (!sata::plan_backward(D, BH, n, d_k, d_v, P, chunk, kMaxBackwardWorkspace, &plan, &fwd))
+    return fail(SATA_ERR_UNSUPPORTED, "no backward slice fits on chip for d_k=%d d_v=%d chunk=%d", d_k, d_v, chunk);
+  hipStream_t s = (hipStream_t)stream;
+  if (way == Way::kPairs && !backward_direct_covers(n, P))
+    return fail(SATA_ERR_UNSUPPORTED, "no pair-by-pair backward for n=%d P=%d", n, P);
+  if (way == Way::kPairs || (way == Way::kEstimate && backward_direct_pays(dt, n, d_k, d_v, P, D))) {
+    void* ws = nullptr;
+    if ((st = get_workspace(sata::backward_direct_bytes(BH, n), s, &ws)) != SATA_OK) return st;
+    hipError_t e = sata::launch_backward_direct(q, k, v, dy, dq, dk, dv, dt == SATA_BF16, BH, n, d_k, d_v, P,
+                                                (float*)ws, s);
+    if (e != hipSuccess) return hip_fail(e, "backward (pair by pair) launch");
+    return ok();
+  }
+  sata::DevTable t;
+  if ((st = get_table(d_k, P, s, &t)) != SATA_OK) return st;
+  void* ws = nullptr;
+  if ((st = get_workspace(plan.h_bytes + plan.state_bytes + plan.partial_bytes, s, &ws)) != SATA_OK) return st;
+  float* h = (float*)ws;
+  float* state = (float*)((char*)ws + plan.h_bytes);
+  float* partial = (float*)((char*)ws + plan.h_bytes + plan.state_bytes);
+  hipError_t e = sata::launch_backward(q, k, v, dy, dq, dk, dv, dt == SATA_BF16, BH, n, d_k, d_v, P, chunk, t, plan,
+                                       fwd, h, state, partial, s);
+  if (e != hipSuccess) return hip_fail(e, "backward launch");
+  return ok();
+}
+
 }  // namespace
 
 extern "C" {
@@ -638,81 +726,58 @@ sata_status sata_prefill_parts(sata_dtype dt, int B, int H, int n, int d_k, int 
 
 sata_status sata_prefill(const void* q, const void* k, const void* v, sata_dtype dt, int B, int H, int n,
                          int d_k, int d_v, int P, int chunk, void* y, float* S_out, void* stream) {
-  int64_t D = 0;
-  sata_status st = check_prefill_args(dt, B, H, n, d_k, d_v, P, chunk, &D);
-  if (st != SATA_OK) return st;
-  if (n > 0 && (!q || !k || !v || !y)) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
-  if (n > 0 && direct_pays(dt, B * H, n, d_k, d_v, P, chunk, D))
-    return prefill_direct(q, k, v, dt, B * H, 1, n, d_k, d_v, P, y, S_out, (hipStream_t)stream, D);
-  return prefill_dispatch(q, k, v, dt, B * H, n, d_k, d_v, P, chunk, y, S_out, (hipStream_t)stream, D, 1);
+  return prefill(Way::kEstimate, q, k, v, dt, B, H, 1, n, d_k, d_v, P, chunk, y, S_out, stream);
 }
 
 sata_status sata_prefill_grouped(const void* q, const void* k, const void* v, sata_dtype dt, int B, int H_kv,
                                  int G, int n, int d_k, int d_v, int P, int chunk, void* y, float* S_out,
                                  void* stream) {
-  if (G < 1) return fail(SATA_ERR_INVALID_ARG, "G=%d must be >= 1", G);
-  if (B >= 1 && H_kv >= 1 && (int64_t)B * H_kv * G > kMaxHeads)
-    return fail(SATA_ERR_TOO_LARGE, "B*H_kv*G=%lld exceeds %d", (long long)B * H_kv * G, kMaxHeads);
-  int64_t D = 0;
-  sata_status st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D);
+  sata_status st = check_groups(B, H_kv, G);
   if (st != SATA_OK) return st;
-  if (n > 0 && (!q || !k || !v || !y)) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
-  if (n > 0 && direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D))
-    return prefill_direct(q, k, v, dt, B * H_kv, G, n, d_k, d_v, P, y, S_out, (hipStream_t)stream, D);
-  const size_t esz = dt == SATA_BF16 ? 2 : 4;
-  // query head g + G h of each batch row is member g of key/value head h's
-  // group: with the heads of the call numbered by key/value head, member g's
-  // queries and outputs start g heads in and lie G heads apart
-  for (int g = 0; g < G; ++g) {
-    const void* qg = (const char*)q + esz * (size_t)g * (size_t)n * (size_t)d_k;
-    void* yg = (char*)y + esz * (size_t)g * (size_t)n * (size_t)d_v;
-    st = prefill_dispatch(qg, k, v, dt, B * H_kv, n, d_k, d_v, P, chunk, yg, g == 0 ? S_out : nullptr,
-                          (hipStream_t)stream, D, G);
-    if (st != SATA_OK) return st;
-    if (n == 0) break;
-  }
+  return prefill(Way::kEstimate, q, k, v, dt, B, H_kv, G, n, d_k, d_v, P, chunk, y, S_out, stream);
+}
+
+sata_status sata_testing_prefill(int pairs, const void* q, const void* k, const void* v, sata_dtype dt, int B,
+                                 int H_kv, int G, int n, int d_k, int d_v, int P, int chunk, void* y, float* S_out,
+                                 void* stream) {
+  sata_status st = check_groups(B, H_kv, G);
+  if (st != SATA_OK) return st;
+  return prefill(pairs ? Way::kPairs : Way::kScan, q, k, v, dt, B, H_kv, G, n, d_k, d_v, P, chunk, y, S_out, stream);
+}
+
+sata_status sata_testing_prefill_route(sata_dtype dt, int B, int H_kv, int G, int n, int d_k, int d_v, int P,
+                                       int chunk, int want_state, sata_route* route) {
+  if (!route) return fail(SATA_ERR_INVALID_ARG, "null output pointer");
+  sata_status st = check_groups(B, H_kv, G);
+  if (st != SATA_OK) return st;
+  int64_t D = 0;
+  if ((st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D)) != SATA_OK) return st;
+  static const sata_route kScans[] = {SATA_ROUTE_MFMA32, SATA_ROUTE_BLOCKS, SATA_ROUTE_FEATURES, SATA_ROUTE_FLOAT32};
+  *route = direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D, want_state != 0,
+                       vector_rows(nullptr, nullptr, nullptr, dt, d_k, d_v))
+               ? SATA_ROUTE_PAIRS
+               : kScans[(int)prefill_path(dt, B * H_kv, n, d_k, d_v, P, chunk)];
   return ok();
 }
 
 sata_status sata_backward(const void* q, const void* k, const void* v, const void* dy, sata_dtype dt, int B, int H,
                           int n, int d_k, int d_v, int P, int chunk, void* dq, void* dk, void* dv, void* stream) {
-  if (!valid_dtype(dt)) return fail(SATA_ERR_INVALID_ARG, "unknown dtype %d", (int)dt);
-  if (B < 1 || H < 1) return fail(SATA_ERR_INVALID_ARG, "B=%d H=%d must be >= 1", B, H);
-  if (n < 0) return fail(SATA_ERR_INVALID_ARG, "n=%d < 0", n);
+  return backward(Way::kEstimate, q, k, v, dy, dt, B, H, n, d_k, d_v, P, chunk, dq, dk, dv, stream);
+}
+
+sata_status sata_testing_backward(int pairs, const void* q, const void* k, const void* v, const void* dy,
+                                  sata_dtype dt, int B, int H, int n, int d_k, int d_v, int P, int chunk, void* dq,
+                                  void* dk, void* dv, void* stream) {
+  return backward(pairs ? Way::kPairs : Way::kScan, q, k, v, dy, dt, B, H, n, d_k, d_v, P, chunk, dq, dk, dv, stream);
+}
+
+sata_status sata_testing_backward_route(sata_dtype dt, int B, int H, int n, int d_k, int d_v, int P, int chunk,
+                                        sata_route* route) {
+  if (!route) return fail(SATA_ERR_INVALID_ARG, "null output pointer");
   int64_t D = 0;
-  sata_status st = check_dims(d_k, d_v, P, &D);
+  sata_status st = check_backward_args(dt, B, H, n, d_k, d_v, P, chunk, &D);
   if (st != SATA_OK) return st;
-  if ((int64_t)B * H > kMaxHeads) return fail(SATA_ERR_TOO_LARGE, "B*H=%lld exceeds %d", (long long)B * H, kMaxHeads);
-  if (chunk != 16 && chunk != 32 && chunk != 64)
-    return fail(SATA_ERR_UNSUPPORTED, "chunk=%d; the backward supports 16, 32, 64", chunk);
-  if (d_k > sata::kMaxBackwardDim || d_v > sata::kMaxBackwardDim)
-    return fail(SATA_ERR_UNSUPPORTED, "the backward supports d_k, d_v <= %d", sata::kMaxBackwardDim);
-  if (n == 0) return ok();
-  if (!q || !k || !v || !dy || !dq || !dk || !dv) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
-  const int BH = B * H;
-  sata::BackwardPlan plan;
-  sata::PrefillGenericPlan fwd;
-  if (!sata::plan_backward(D, BH, n, d_k, d_v, P, chunk, kMaxBackwardWorkspace, &plan, &fwd))
-    return fail(SATA_ERR_UNSUPPORTED, "no backward slice fits on chip for d_k=%d d_v=%d chunk=%d", d_k, d_v, chunk);
-  hipStream_t s = (hipStream_t)stream;
-  if (backward_direct_pays(dt, n, d_k, d_v, P, D)) {
-    void* ws = nullptr;
-    if ((st = get_workspace(sata::backward_direct_bytes(BH, n), s, &ws)) != SATA_OK) return st;
-    hipError_t e = sata::launch_backward_direct(q, k, v, dy, dq, dk, dv, dt == SATA_BF16, BH, n, d_k, d_v, P,
-                                                (float*)ws, s);
-    if (e != hipSuccess) return hip_fail(e, "backward (pair by pair) launch");
-    return ok();
-  }
-  sata::DevTable t;
-  if ((st = get_table(d_k, P, s, &t)) != SATA_OK) return st;
-  void* ws = nullptr;
-  if ((st = get_workspace(plan.h_bytes + plan.state_bytes + plan.partial_bytes, s, &ws)) != SATA_OK) return st;
-  float* h = (float*)ws;
-  float* state = (float*)((char*)ws + plan.h_bytes);
-  float* partial = (float*)((char*)ws + plan.h_bytes + plan.state_bytes);
-  hipError_t e = sata::launch_backward(q, k, v, dy, dq, dk, dv, dt == SATA_BF16, BH, n, d_k, d_v, P, chunk, t, plan,
-                                       fwd, h, state, partial, s);
-  if (e != hipSuccess) return hip_fail(e, "backward launch");
+  *route = backward_direct_pays(dt, n, d_k, d_v, P, D) ? SATA_ROUTE_PAIRS : SATA_ROUTE_FLOAT32;
   return ok();
 }
 
