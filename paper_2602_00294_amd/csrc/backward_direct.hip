@@ -25,6 +25,12 @@
 // inputs are exact operands; float32 values (float32 inputs, w / Z and g) are
 // carried as three bfloat16 numbers (24 bits) and a product of two as the six
 // partial products of order 2^-16 and up, accumulated in float32.
+//
+// Values that are not finite stay with the tokens that depend on them.  Only a
+// row's own chunk holds masked pairs, and a masked weight's zero times an
+// infinity or NaN would reach the sum, so steps of an own chunk look at their
+// rows' exponents and, if one is not finite, contract with its entries left out
+// (0 to 3% of the time, 9% at most: d_k = 64, P = 4, 128 tokens).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -106,6 +112,11 @@ struct RowStage {
     const uint32_t chunk = (uint32_t)c * (uint32_t)(kCh * width * (int)sizeof(T));
 #pragma unroll
     for (int i = 0; i < L::kIt; ++i) r[i] = read(from[i] + chunk);
+  }
+  __device__ float entry(int row, int col) const {
+    const T x = base[(int64_t)row * width + col];
+    if constexpr (sizeof(T) == 4) return x;
+    else return __uint_as_float((uint32_t)x << 16);
   }
   __device__ static void put_elem(u16* dst, T x) {
     if constexpr (sizeof(T) == 4) {
@@ -205,10 +216,17 @@ __device__ __forceinline__ void split3(float (&x)[8], uint4 (&b)[3]) {
   }
 }
 
-// acc[j] += (column tile j of the staged rows 32 s .. +31)^T times b
+// The entries of a plane that are infinite or NaN, all bits of each set.
+__device__ __forceinline__ uint4 not_finite_entries(const uint4& w) {
+  auto wide = [](uint32_t x) { return ((((x & 0x7f807f80u) + 0x00800080u) & 0x80008000u) >> 15) * 0xffffu; };
+  return uint4{wide(w.x), wide(w.y), wide(w.z), wide(w.w)};
+}
+
+// acc[j] += (column tile j of the staged rows 32 s .. +31)^T times b; entries
+// that are not finite count as zero if `clean`
 template <typename T, int DT>
 __device__ __forceinline__ void contract(const u16* rows, int s, int l15, int g4, const uint4 (&b)[3],
-                                         f32x4 (&acc)[DT]) {
+                                         f32x4 (&acc)[DT], bool clean = false) {
   using L = BwdLayout<T, DT>;
   const u16* const p = rows + (32 * s + 4 * g4 + (l15 >> 2)) * L::kRS + 4 * (l15 & 3);
 #pragma unroll
@@ -216,8 +234,27 @@ __device__ __forceinline__ void contract(const u16* rows, int s, int l15, int g4
     uint4 a[L::kPl];
 #pragma unroll
     for (int pl = 0; pl < L::kPl; ++pl) a[pl] = read_transposed(p + pl * L::kPlane + 16 * j, 16 * L::kRS);
+    if (clean) {
+      const uint4 m = not_finite_entries(a[0]);
+#pragma unroll
+      for (int pl = 0; pl < L::kPl; ++pl) a[pl].x &= ~m.x, a[pl].y &= ~m.y, a[pl].z &= ~m.z, a[pl].w &= ~m.w;
+    }
     acc[j] = dot_planes(a, b, acc[j]);
   }
+}
+
+// Bits set where one of the rows' entries (16 rows in their first plane, as
+// load_rows gives them) has the exponent of infinities and NaN.
+template <int KS, int PL>
+__device__ __forceinline__ uint32_t not_finite(const uint4 (&f)[KS][PL]) {
+  uint32_t bits = 0;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const uint32_t w[4] = {f[ks][0].x, f[ks][0].y, f[ks][0].z, f[ks][0].w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bits |= (w[i] & 0x7f807f80u) + 0x00800080u;
+  }
+  return bits & 0x80008000u;
 }
 
 // Where a chunk's contractions are summed: in `chunk`, from zero, with three
@@ -276,8 +313,10 @@ __device__ __forceinline__ bool locate(const BwdArgs& a, int& head, int& blk) {
   return true;
 }
 
+// (waves per SIMD: as many as the working registers allow without the rare
+// handling of values that are not finite)
 template <typename T, int DT, int NQ, int PP>
-__global__ void __launch_bounds__(kNW * 64, 2) backward_rows(BwdArgs a) {
+__global__ void __launch_bounds__(kNW * 64, sizeof(T) == 2 ? 3 : 2) backward_rows(BwdArgs a) {
   using L = BwdLayout<T, DT>;
   extern __shared__ __attribute__((aligned(16))) u16 smem16[];
   const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, g4 = lane >> 4;
@@ -332,14 +371,16 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_rows(BwdArgs a) {
       __syncthreads();
     }
   };
-  // u and a of query tile i against keys 32 s .. +31 (4 h + r: key 32 s + 16 h + 4 g4 + r)
-  auto pairs = [&](const u16* kb, const u16* vb, int s, auto ic, float (&u)[8], float (&av)[8]) {
+  // u and a of query tile i against keys 32 s .. +31 (4 h + r: key 32 s + 16 h + 4 g4 + r);
+  // bad: bits for keys that are not finite
+  auto pairs = [&](const u16* kb, const u16* vb, int s, auto ic, float (&u)[8], float (&av)[8], uint32_t& bad) {
     constexpr int I = decltype(ic)::value;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       uint4 f[L::kKS][L::kPl];
       load_rows<T, DT>(kb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
       const f32x4 x = dot_rows(f, qf[I], a.se.shift);
+      bad |= not_finite(f);
       load_rows<T, DT>(vb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
       const f32x4 y = dot_rows(f, df[I], 0.f);
 #pragma unroll
@@ -367,9 +408,13 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_rows(BwdArgs a) {
     const int steps = kOwn ? (wave >> 1) + 1 : 2;
     for (int s = 0; s < steps; ++s) {
       float u[8], av[8], w[8];
-      pairs(kb, vb, s, ic, u, av);
+      uint32_t bad = 0;
+      pairs(kb, vb, s, ic, u, av, bad);
       series_eval<MM>(m, u, w, a.se.e, lw);
-      if (kOwn) masked(s, w);
+      if (kOwn) {
+        masked(s, w);
+        masked(s, av);  // (0 * av would carry a value that is not finite to earlier queries)
+      }
       float zs = 0.f, ms = 0.f;  // (a step's sums first: fewer roundings of the long sums)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -390,7 +435,8 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_rows(BwdArgs a) {
     ma[i] += __shfl_xor(ma[i], 32);
     const int c = c_first + i;
     const bool ok = c * kCh + 16 * wave + l15 < n;
-    const float rz = ok ? 1.f / z[i] : 0.f;
+    // (z - z: a sum that is not finite leaves no gradient finite, not even 1 / z = 0)
+    const float rz = ok ? 1.f / z[i] + (z[i] - z[i]) : 0.f;
     mu[i] = ok ? ma[i] / z[i] : 0.f;
     rg[i] = rz * (float)m;
     if (g4 == 0 && c < nch) {
@@ -415,14 +461,17 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_rows(BwdArgs a) {
     f32x4(&sum)[DT] = chunk_sum<L::kPl>(chunk, acc[I]);
     for (int s = 0; s < steps; ++s) {
       float u[8], av[8], g[8];
-      pairs(kb, vb, s, ic, u, av);
+      uint32_t bad = 0;
+      pairs(kb, vb, s, ic, u, av, bad);
       series_eval<DM>(m - 1, u, g, a.se.de, ld);
 #pragma unroll
       for (int e = 0; e < 8; ++e) g[e] *= av[e] - mu[I];
       if (kOwn) masked(s, g);
       uint4 b[3];
       split3(g, b);
-      contract<T, DT>(kb, s, l15, g4, b, sum);
+      // (a later key that is not finite times a masked zero is no zero; without
+      // it, an earlier one still reaches dq, through g)
+      contract<T, DT>(kb, s, l15, g4, b, sum, kOwn && __ballot(bad));
     }
     add_chunk<L::kPl>(chunk, acc[I]);
   });
@@ -434,7 +483,8 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_rows(BwdArgs a) {
 }
 
 template <typename T, int DT, int NQ, int PP>
-__global__ void __launch_bounds__(kNW * 64, 2) backward_cols(BwdArgs a) {
+__global__ void __launch_bounds__(kNW * 64, sizeof(T) == 2 && DT <= 2 ? (DT == 1 && NQ == 1 ? 4 : 3) : 2)
+backward_cols(BwdArgs a) {
   using L = BwdLayout<T, DT>;
   extern __shared__ __attribute__((aligned(16))) u16 smem16[];
   const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, g4 = lane >> 4;
@@ -478,6 +528,7 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_cols(BwdArgs a) {
     sy.put(base + L::kTensor, c);
     if (tid < 3 * kCh / 4) ((float4*)(base + 2 * L::kTensor))[tid] = rs;
   };
+  bool dirty = false;  // whether own chunks had entries left out
   // key tile i against the queries of a staged chunk
   auto work = [&](const u16* base, auto ic, auto own) {
     constexpr int I = decltype(ic)::value;
@@ -490,12 +541,15 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_cols(BwdArgs a) {
     f32x4(&sumv)[DT] = chunk_sum<L::kPl>(cv, dva[I]);
     for (int s = kOwn ? wave >> 1 : 0; s < 2; ++s) {
       float u[8], av[8], w[8], g[8];
+      uint32_t bad = 0;  // a query or a gradient of the step that is not finite
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         uint4 f[L::kKS][L::kPl];
         load_rows<T, DT>(qb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
         const f32x4 x = dot_rows(f, kf[I], a.se.shift);
+        if (kOwn) bad |= not_finite(f);
         load_rows<T, DT>(yb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
+        if (kOwn) bad |= not_finite(f);
         const f32x4 y = dot_rows(f, vf[I], 0.f);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -519,11 +573,16 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_cols(BwdArgs a) {
           if (kOwn && at + r < 16 * wave + l15) w[4 * h + r] = g[4 * h + r] = 0.f;
         }
       }
+      // (an earlier query or gradient that is not finite times a masked zero is no
+      // zero; without it, later ones still reach dk and dv, queries through w and
+      // g, gradients through g and, column by column, at the end)
+      const bool clean = kOwn && __ballot(bad);
+      dirty |= clean;
       uint4 b[3];
       split3(w, b);
-      contract<T, DT>(yb, s, l15, g4, b, sumv);
+      contract<T, DT>(yb, s, l15, g4, b, sumv, clean);
       split3(g, b);
-      contract<T, DT>(qb, s, l15, g4, b, sumk);
+      contract<T, DT>(qb, s, l15, g4, b, sumk, clean);
     }
     add_chunk<L::kPl>(ck, dka[I]);
     add_chunk<L::kPl>(cv, dva[I]);
@@ -548,6 +607,16 @@ __global__ void __launch_bounds__(kNW * 64, 2) backward_cols(BwdArgs a) {
   for (int i = 0; i < NQ; ++i) {
     const int row = (c_first + i) * kCh + 16 * wave + l15;
     if (row >= n) continue;
+    if (dirty) {  // gradients of the own chunk that are not finite, for the keys at or before them
+      for (int other = row; other < min(n, (c_first + i + 1) * kCh); ++other)
+#pragma unroll
+        for (int j = 0; j < DT; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int col = 16 * j + 4 * g4 + r;
+            if (col < dv) dva[i][j][r] += sy.entry(other, col) * 0.f;
+          }
+    }
     store_row<T, DT>((T*)a.dk + ((int64_t)head * n + row) * dk, dk, g4, dka[i], 1.f);
     store_row<T, DT>((T*)a.dv + ((int64_t)head * n + row) * dv, dv, g4, dva[i], 1.f);
   }

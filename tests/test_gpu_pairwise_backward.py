@@ -14,6 +14,7 @@ import numpy as np
 import pytest
 
 import oracle
+import routes
 import sata_synth as syn
 from gpu_util import to_dev, to_host
 
@@ -106,3 +107,32 @@ def test_scan_backward_of_long_sequences(sata, n, dk, dv, P, dtype):
     got = [to_host(x)[0, 0] for x in sata.backward(*(to_dev(a, dtype) for a in (q, k, v, dy)), P)]
     torch.cuda.synchronize()
     _check(got, q[0, 0], k[0, 0], v[0, 0], dy[0, 0], P, 2 ** -8 if dtype == "bf16" else 1e-4, "scan")
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n,dk,dv,P,dtype", [(140, 16, 16, 4, "bf16"), (100, 24, 40, 3, "bf16"), (70, 64, 64, 2, "bf16"),
+                                             (140, 16, 16, 4, "f32"), (100, 24, 40, 3, "f32"), (70, 48, 64, 5, "f32")])
+def test_pairwise_backward_keeps_nonfinite_tokens_to_those_that_depend_on_them(sata, n, dk, dv, P, dtype, value):
+    """Head t has one entry of token t that is not finite.  Gradients that do not
+    depend on it are bitwise those without it; those that do are not finite."""
+    print(f"pairwise backward, {value} n={n} dk={dk} dv={dv} P={P} {dtype}", file=sys.stderr, flush=True)
+    one = [to_dev(a, dtype) for a in _inputs(460 + n, 1, 1, n, dk, dv, dtype)]
+    clean = [g[0, 0] for g in routes.backward_by(True, *one, P)]
+    t, c = torch.arange(n, device="cuda"), 2
+    head, row = t[:, None], t[None, :]      # masks [head, row]
+    never, always = head < 0, head >= 0
+    # rows of dq, dk, dv that depend on the entry, and whether dv does in column c alone
+    depend = {"q": (row == head, row <= head, row <= head, False), "k": (row >= head, always, always, False),
+              "v": (row >= head, always, never, False), "dy": (row == head, row <= head, row <= head, True)}
+    for i, name in enumerate(("q", "k", "v", "dy")):
+        x = [a.expand(1, n, *a.shape[2:]).contiguous() for a in one]
+        x[i][0, t, t, c] = value
+        got = routes.backward_by(True, *x, P)
+        torch.cuda.synchronize()
+        for j, (what, g, want) in enumerate(zip(("dq", "dk", "dv"), got, clean)):
+            bad = depend[name][j].expand(n, n)[..., None].expand(n, n, want.shape[-1]).clone()
+            if what == "dv" and depend[name][3]:
+                bad &= torch.arange(want.shape[-1], device="cuda") == c
+            label = f"{name}: {what}"
+            assert not torch.isfinite(g[0][bad]).any(), label
+            assert torch.equal(g[0][~bad], want.expand(n, *want.shape)[~bad]), label
