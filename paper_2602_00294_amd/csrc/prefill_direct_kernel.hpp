@@ -434,7 +434,10 @@ prefill_direct_kernel(const T* __restrict__ q_, const T* __restrict__ k_, const 
         const uint4 b2 = to_bf16(w);
 #pragma unroll
         for (int j = 0; j < NCT; ++j) {
-          const uint4 va = load_vt(vb, s, j);
+          uint4 va = load_vt(vb, s, j);
+          // (a step's second 16 keys are all masked for the tile of its first 16
+          // queries; a value there that is not finite would not be zero times 0)
+          if (2 * s == wave) va.z = va.w = 0u;
           O[i][j] = mfma_bf16(va, b2, O[i][j]);
           O[i][j] = mfma_bf16(va, b1, O[i][j]);
           O[i][j] = mfma_bf16(va, b0, O[i][j]);

@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import oracle
+import routes
 import sata_synth as syn
 from gpu_util import check_prefill_head, check_rows, check_state, operands, to_dev, to_host, y_tol
 
@@ -134,6 +135,27 @@ def test_pairwise_prefill_keeps_nonfinite_tokens_to_later_chunks(sata, dtype):
     assert torch.equal(yk[0, 0, :128], y0[0, 0, :128]) and torch.isnan(yk[0, 0, 150:]).all()
     keep = [t for t in range(n) if t != 150]
     assert torch.equal(yq[0, 0, keep], y0[0, 0, keep]) and torch.isnan(yq[0, 0, 150]).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,dk,dv,P", [(130, 16, 16, 4), (100, 48, 64, 2)])
+def test_pairwise_prefill_keeps_nonfinite_values_to_their_tile(sata, n, dk, dv, P, dtype):
+    """Head t has a NaN in column 2 of token t's value: the other columns, and the
+    rows of earlier tiles of 16 tokens, are bitwise those without it, and the
+    rows from t on NaN (the scans keep to the same tiles)."""
+    print(f"pairwise prefill, NaN values n={n} dk={dk} dv={dv} P={P} {dtype}", file=sys.stderr, flush=True)
+    one = [to_dev(a, dtype) for a in _inputs(560 + n, 1, 1, n, dk, dv, dtype)]
+    clean = routes.prefill_by(True, *one, P, want_state=False)[0][0, 0]
+    q, k, v = (a.expand(1, n, *a.shape[2:]).contiguous() for a in one)
+    t = torch.arange(n, device="cuda")
+    v[0, t, t, 2] = float("nan")
+    y = routes.prefill_by(True, q, k, v, P, want_state=False)[0][0]
+    torch.cuda.synchronize()
+    others = [c for c in range(dv) if c != 2]
+    assert torch.equal(y[..., others], clean[:, others].expand(n, n, dv - 1))
+    earlier = t[None, :] < 16 * (t[:, None] // 16)
+    assert torch.equal(y[..., 2][earlier], clean[:, 2].expand(n, n)[earlier])
+    assert torch.isnan(y[..., 2][t[None, :] >= t[:, None]]).all()
 
 
 @pytest.mark.parametrize("B,H,n,d,P,dtype", [
