@@ -160,9 +160,10 @@ struct RowStage {
   }
 };
 
-// B operands of one own row per lane: entries 32 ks + 8 g4 .. +7, all planes.
+// B operands of one own row per lane times a power of two: entries 32 ks + 8 g4
+// .. +7, all planes.
 template <typename T, int DT>
-__device__ __forceinline__ void load_own(const T* p, bool ok, int width, int g4,
+__device__ __forceinline__ void load_own(const T* p, bool ok, int width, int g4, float scale,
                                          uint4 (&f)[BwdLayout<T, DT>::kKS][BwdLayout<T, DT>::kPl]) {
   using L = BwdLayout<T, DT>;
 #pragma unroll
@@ -171,7 +172,7 @@ __device__ __forceinline__ void load_own(const T* p, bool ok, int width, int g4,
     if constexpr (sizeof(T) == 4) {
       float x[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = ok && c0 + j < width ? p[c0 + j] : 0.f;
+      for (int j = 0; j < 8; ++j) x[j] = ok && c0 + j < width ? p[c0 + j] * scale : 0.f;
 #pragma unroll
       for (int pl = 0; pl < L::kPl; ++pl) {
         f[ks][pl] = to_bf16(x);
@@ -182,6 +183,8 @@ __device__ __forceinline__ void load_own(const T* p, bool ok, int width, int g4,
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         if (ok && c0 + j < width) u[j >> 1] |= (uint32_t)p[c0 + j] << (16 * (j & 1));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) u[j] = pack2(lo_f32(u[j]) * scale, hi_f32(u[j]) * scale);
       f[ks][0] = uint4{u[0], u[1], u[2], u[3]};
     }
   }
@@ -234,7 +237,7 @@ __device__ __forceinline__ void contract(const u16* rows, int s, int l15, int g4
     uint4 a[L::kPl];
 #pragma unroll
     for (int pl = 0; pl < L::kPl; ++pl) a[pl] = read_transposed(p + pl * L::kPlane + 16 * j, 16 * L::kRS);
-    if (clean) {
+    if (__builtin_expect(clean, 0)) {
       const uint4 m = not_finite_entries(a[0]);
 #pragma unroll
       for (int pl = 0; pl < L::kPl; ++pl) a[pl].x &= ~m.x, a[pl].y &= ~m.y, a[pl].z &= ~m.z, a[pl].w &= ~m.w;
@@ -294,7 +297,7 @@ __device__ __forceinline__ void store_row(T* p, int width, int g4, const f32x4 (
 struct BwdArgs {
   const void *q, *k, *v, *dy;
   void *dq, *dk, *dv;
-  float* stat;  // [head][chunk][3][64]: 1 / Z, (P-1) / Z, -mu (P-1) / Z (in units of kappa)
+  float* stat;  // [head][chunk][3][64]: 1 / Z, (P-1) / Z, -mu (P-1) / Z (in the series' units)
   Series se;
   int heads, n, dk_, dv_, P, blocks, by_xcd;
 };
@@ -342,8 +345,8 @@ __global__ void __launch_bounds__(kNW * 64, sizeof(T) == 2 ? 3 : 2) backward_row
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
     const int row = (c_first + i) * kCh + 16 * wave + l15;
-    load_own<T, DT>(qp + (int64_t)row * dk, row < n, dk, g4, qf[i]);
-    load_own<T, DT>(dyp + (int64_t)row * dv, row < n, dv, g4, df[i]);
+    load_own<T, DT>(qp + (int64_t)row * dk, row < n, dk, g4, a.se.scale, qf[i]);
+    load_own<T, DT>(dyp + (int64_t)row * dv, row < n, dv, g4, 1.f, df[i]);
   }
   // work(K rows, V rows, tile, on its own chunk) for every key chunk and query tile
   auto sweep = [&](auto&& work) {
@@ -438,7 +441,7 @@ __global__ void __launch_bounds__(kNW * 64, sizeof(T) == 2 ? 3 : 2) backward_row
     // (z - z: a sum that is not finite leaves no gradient finite, not even 1 / z = 0)
     const float rz = ok ? 1.f / z[i] + (z[i] - z[i]) : 0.f;
     mu[i] = ok ? ma[i] / z[i] : 0.f;
-    rg[i] = rz * (float)m;
+    rg[i] = rz * ((float)m * a.se.scale);
     if (g4 == 0 && c < nch) {
       float* const p = stat + (int64_t)c * 3 * kCh + 16 * wave + l15;
       p[0] = rz;
@@ -511,8 +514,8 @@ backward_cols(BwdArgs a) {
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
     const int row = (c_first + i) * kCh + 16 * wave + l15;
-    load_own<T, DT>(kp + (int64_t)row * dk, row < n, dk, g4, kf[i]);
-    load_own<T, DT>(vp + (int64_t)row * dv, row < n, dv, g4, vf[i]);
+    load_own<T, DT>(kp + (int64_t)row * dk, row < n, dk, g4, a.se.scale, kf[i]);
+    load_own<T, DT>(vp + (int64_t)row * dv, row < n, dv, g4, 1.f, vf[i]);
 #pragma unroll
     for (int j = 0; j < DT; ++j) dka[i][j] = dva[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }

@@ -136,7 +136,8 @@ prefill_direct_kernel(const T* __restrict__ q_, const T* __restrict__ k_, const 
     }
   }
 
-  // ---- this wave's queries: B operands of the scores, lane = query l15
+  // ---- this wave's queries: B operands of the scores, lane = query l15, in the
+  // series' units
   constexpr int kQP = X3 ? 3 : 1;  // packed: [qh|qh], [qm|qm], [ql|qh]
   uint4 qf[NQ][NKT][kQP];
 #pragma unroll
@@ -148,7 +149,7 @@ prefill_direct_kernel(const T* __restrict__ q_, const T* __restrict__ k_, const 
       if constexpr (X3) {
         float x[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = row < n && c0 + j < dk ? qp[(int64_t)row * dk + c0 + j] : 0.f;
+        for (int j = 0; j < 8; ++j) x[j] = row < n && c0 + j < dk ? qp[(int64_t)row * dk + c0 + j] * se.scale : 0.f;
 #pragma unroll
         for (int pl = 0; pl < kQP; ++pl) {
           qf[i][kt][pl] = to_bf16(x);
@@ -168,7 +169,8 @@ prefill_direct_kernel(const T* __restrict__ q_, const T* __restrict__ k_, const 
             w = uint4{u[0], u[1], u[2], u[3]};
           }
         }
-        qf[i][kt][0] = w;
+        auto scaled = [&](uint32_t u) { return pack2(lo_f32(u) * se.scale, hi_f32(u) * se.scale); };
+        qf[i][kt][0] = uint4{scaled(w.x), scaled(w.y), scaled(w.z), scaled(w.w)};
       }
     }
   }
@@ -320,7 +322,8 @@ prefill_direct_kernel(const T* __restrict__ q_, const T* __restrict__ k_, const 
       for (int pl = 0; pl < L::kPk; ++pl)
         ka[kt][pl] = *(const uint4*)(kb + pl * L::kKPlane + (32 * s + 16 * h + l15) * KS + 32 * kt + 8 * g4);
   };
-  // u = score + sqrt(d_k) of query tile i against 16 keys (smallest products first)
+  // u = score + sqrt(d_k), in the series' units, of query tile i against 16 keys
+  // (smallest products first)
   auto scores = [&](const uint4 (&ka)[NKT][L::kPk], int i, float* u) {
     f32x4 a = {se.shift, se.shift, se.shift, se.shift};
 #pragma unroll
@@ -389,7 +392,7 @@ prefill_direct_kernel(const T* __restrict__ q_, const T* __restrict__ k_, const 
         for (int kk = 0; kk < dk; kk += 4) {
           const int col = kk + g4;
           const float xk = (key < n && col < dk) ? (float)kp[(int64_t)key * dk + col] : 0.f;
-          const float xq = (row < n && col < dk) ? (float)qp[(int64_t)row * dk + col] : 0.f;
+          const float xq = (row < n && col < dk) ? (float)qp[(int64_t)row * dk + col] * se.scale : 0.f;
           a = mfma_f32(xk, xq, a);
         }
         float x[4], w[4];

@@ -10,7 +10,11 @@
 //     kappa f_P = u^m + e_{m-2} u^{m-2} + ... + e_0,  e_j = a_j d_k^((m-j)/2),
 //     kappa = m! d_k^(m/2).
 // The factor kappa is the same for every pair and leaves with the
-// normalisation.
+// normalisation.  It is up to 1e10 (P = 8, d_k = 64) and would take as much from
+// the range of the scores, so r comes in units of 2^x (one operand's rows are
+// scaled, exactly), with 2^x near kappa^(1/m): then all of u, e_j and the sum are
+// scaled by powers of two, the results are the same bits, and the factor left on
+// f_P is within 2^(+-m/2).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -35,10 +39,14 @@ struct Series {
   float e[kMaxSeries];   // e[j] of f_P
   float de[kMaxSeries];  // e[j] of f_{P-1} (the derivative's)
   float shift;           // sqrt(d_k)
+  float scale;           // 2^-x: of the queries (or keys) that make the scores
 };
 
 inline Series make_series(int P, int dk) {
   Series se{};
+  double kappa = 1.0;
+  for (int j = 1; j < P; ++j) kappa *= j * std::sqrt((double)dk);
+  const int x = P > 1 ? (int)std::lround(std::log2(kappa) / (P - 1)) : 0;
   auto fill = [&](int m, float* e) {
     double fact[kMaxSeries];  // m! / j!
     fact[m] = 1.0;
@@ -50,12 +58,13 @@ inline Series make_series(int P, int dk) {
         t /= -(r + 1);
       }
       if (j == m - 1) a = 0.0;  // (1 - 1)
-      e[j] = (float)(fact[j] * a * std::pow((double)dk, 0.5 * (m - j)));
+      e[j] = std::ldexp((float)(fact[j] * a * std::pow((double)dk, 0.5 * (m - j))), -x * (m - j));
     }
   };
   fill(P - 1, se.e);
   if (P > 1) fill(P - 2, se.de);
-  se.shift = (float)std::sqrt((double)dk);
+  se.shift = std::ldexp((float)std::sqrt((double)dk), -x);
+  se.scale = std::ldexp(1.f, -x);
   return se;
 }
 

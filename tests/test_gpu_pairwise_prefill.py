@@ -3,6 +3,7 @@ and of the state summed over the tokens (prefill_state.hip) at the edges of
 their tiles, against the float64 oracle, with the bounds of the arithmetic that
 the library reports for the call; and of the scan kernels at the lengths that
 they still serve."""
+import math
 import sys
 
 import numpy as np
@@ -135,6 +136,32 @@ def test_pairwise_prefill_keeps_nonfinite_tokens_to_later_chunks(sata, dtype):
     assert torch.equal(yk[0, 0, :128], y0[0, 0, :128]) and torch.isnan(yk[0, 0, 150:]).all()
     keep = [t for t in range(n) if t != 150]
     assert torch.equal(yq[0, 0, keep], y0[0, 0, keep]) and torch.isnan(yq[0, 0, 150]).all()
+
+
+@pytest.mark.parametrize("dk,P", [(16, 8), (8, 8), (64, 4), (32, 5)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_pairwise_range_of_scores(sata, dtype, dk, P):
+    """Scores so large that f_P nears 2^112: n |v| times that, 2^121, and the
+    factor within 2^(+-3.5) that the kernels leave on the weights are inside
+    float32; (P-1)! d_k^((P-1)/2), at least 2^11 here, would not be."""
+    n, dv = 96, 16
+    print(f"pairwise range dk={dk} P={P} {dtype}", file=sys.stderr, flush=True)
+    q, k, v = (np.abs(a) for a in _inputs(570, 1, 1, n, dk, dv, dtype))
+    dy = _inputs(571, 1, 1, n, dk, dv, dtype)[2]
+    top = np.max(q[0, 0].astype(np.float64) @ k[0, 0].T.astype(np.float64)) / np.sqrt(dk)
+    q = q * np.float32(2.0 ** np.floor(np.log2((2.0 ** 112 * math.factorial(P - 1)) ** (1 / (P - 1)) / top)))
+    dev = [to_dev(a, dtype) for a in (q, k, v, dy)]
+    y, _ = routes.prefill_by(True, *dev[:3], P, want_state=False)
+    grads = routes.backward_by(True, *dev, P)
+    torch.cuda.synchronize()
+    ref, _, kap = oracle.taylor_attention(q[0, 0], k[0, 0], v[0, 0], P)
+    check_rows(to_host(y)[0, 0], ref, kap, y_tol("split" if dtype == "f32" else "bf16", dtype), P, "y")
+    want = oracle.taylor_attention_backward(q[0, 0], k[0, 0], v[0, 0], dy[0, 0], P)
+    for name, g, w in zip(("dq", "dk", "dv"), grads, want):
+        g = to_host(g)[0, 0]
+        assert np.isfinite(g).all(), name
+        # the scores' relative rounding, (P-1) 2^-24, times a - mu's cancellation
+        assert np.linalg.norm(g - w) <= (2 ** -8 if dtype == "bf16" else 1e-5) * np.linalg.norm(w), name
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
