@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <tuple>
 #include <utility>
@@ -55,7 +56,6 @@ struct TableEntry {
 
 // A state-sum work list on a device, one allocation.
 struct StateTableEntry {
-  std::vector<char> host;
   char* ptr = nullptr;
   sata::DevStateTable dev;
 };
@@ -161,49 +161,59 @@ sata_status get_table(int d, int P, hipStream_t stream, sata::DevTable* out) {
 }
 
 // The work list of the state sum for a block shape, uploaded once per device.
+// It is built outside the lock: other calls go on meanwhile.
 sata_status get_state_table(int d, int P, const sata::StateShape& shape, hipStream_t stream,
-                            sata::DevStateTable* out) {
+                            sata::DevStateTable* out) try {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-  std::lock_guard<std::mutex> lock(g_mu);
-  DeviceCache& dc = g_devices[dev];
   const auto key = std::make_tuple(d, P, shape);
-  auto it = dc.state_tables.find(key);
-  if (it == dc.state_tables.end()) {
-    const sata::StateTable st = sata::make_state_table(d, P, shape);
-    StateTableEntry ent;
-    auto put = [&ent](const void* p, size_t bytes) {
-      const size_t at = ent.host.size();
-      ent.host.resize((at + bytes + 255) / 256 * 256);
-      if (bytes) std::memcpy(ent.host.data() + at, p, bytes);
-      return at;
-    };
-    const size_t o_gsym = put(st.gsym.data(), st.gsym.size() * sizeof(st.gsym[0]));
-    const size_t o_list = put(st.list.data(), st.list.size() * sizeof(st.list[0]));
-    const size_t o_ftab = put(st.ftab.data(), st.ftab.size() * sizeof(st.ftab[0]));
-    const size_t o_ztab = put(st.ztab.data(), st.ztab.size() * sizeof(st.ztab[0]));
-    if ((e = hipMalloc(&ent.ptr, ent.host.size() + 256)) != hipSuccess) return hip_fail(e, "hipMalloc(state table)");
-    e = hipMemcpyAsync(ent.ptr, ent.host.data(), ent.host.size(), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-      hipFree(ent.ptr);
-      return hip_fail(e, "uploading the state table");
-    }
-    ent.dev.gsym = (const uint64_t*)(ent.ptr + o_gsym);
-    ent.dev.list = (const sata::StateBlock*)(ent.ptr + o_list);
-    ent.dev.ftab = (const int32_t*)(ent.ptr + o_ftab);
-    ent.dev.ztab = (const int32_t*)(ent.ptr + o_ztab);
-    ent.dev.zcols = st.zcols;
-    ent.dev.tall = st.tall;
-    ent.dev.blocks = st.blocks;
-    ent.dev.zblocks = st.zblocks;
-    ent.host.clear();
-    ent.host.shrink_to_fit();
-    it = dc.state_tables.emplace(key, std::move(ent)).first;
+  auto find = [&]() {
+    DeviceCache& dc = g_devices[dev];
+    auto it = dc.state_tables.find(key);
+    if (it == dc.state_tables.end()) return false;
+    *out = it->second.dev;
+    return true;
+  };
+  {
+    std::lock_guard<std::mutex> lock(g_mu);
+    if (find()) return SATA_OK;
   }
-  *out = it->second.dev;
+  const sata::StateTable st = sata::make_state_table(d, P, shape);
+  std::vector<char> host;
+  auto put = [&host](const void* p, size_t bytes) {
+    const size_t at = host.size();
+    host.resize((at + bytes + 255) / 256 * 256);
+    if (bytes) std::memcpy(host.data() + at, p, bytes);
+    return at;
+  };
+  const size_t o_gsym = put(st.gsym.data(), st.gsym.size() * sizeof(st.gsym[0]));
+  const size_t o_list = put(st.list.data(), st.list.size() * sizeof(st.list[0]));
+  const size_t o_ftab = put(st.ftab.data(), st.ftab.size() * sizeof(st.ftab[0]));
+  const size_t o_ztab = put(st.ztab.data(), st.ztab.size() * sizeof(st.ztab[0]));
+  std::lock_guard<std::mutex> lock(g_mu);
+  if (find()) return SATA_OK;
+  StateTableEntry ent;
+  if ((e = hipMalloc(&ent.ptr, host.size() + 256)) != hipSuccess) return hip_fail(e, "hipMalloc(state table)");
+  e = hipMemcpyAsync(ent.ptr, host.data(), host.size(), hipMemcpyHostToDevice, stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  if (e != hipSuccess) {
+    hipFree(ent.ptr);
+    return hip_fail(e, "uploading the state table");
+  }
+  ent.dev.gsym = (const uint64_t*)(ent.ptr + o_gsym);
+  ent.dev.list = (const sata::StateBlock*)(ent.ptr + o_list);
+  ent.dev.ftab = (const int32_t*)(ent.ptr + o_ftab);
+  ent.dev.ztab = (const int32_t*)(ent.ptr + o_ztab);
+  ent.dev.zcols = st.zcols;
+  ent.dev.tall = st.tall;
+  ent.dev.blocks = st.blocks;
+  ent.dev.zblocks = st.zblocks;
+  *out = ent.dev;
+  g_devices[dev].state_tables.emplace(key, ent);
   return SATA_OK;
+} catch (const std::bad_alloc&) {
+  return fail(SATA_ERR_HIP, "out of host memory for the state table of d_k=%d P=%d", d, P);
 }
 
 // The cached table of (d, P) on the current device, without creating one.

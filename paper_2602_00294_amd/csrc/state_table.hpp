@@ -92,47 +92,85 @@ inline int64_t feature_rank(int d, const int* t, int m) {
   return r;
 }
 
+// cum[r][x]: non-decreasing r-tuples over symbols y..d-1, summed over y < x (the
+// steps of feature_rank).
+struct RankSums {
+  std::vector<int64_t> cum[kMaxP];
+  int64_t base[kMaxP + 1] = {0};  // features of lower degrees
+  explicit RankSums(int d) {
+    for (int r = 0; r < kMaxP; ++r) {
+      cum[r].assign((size_t)d + 1, 0);
+      for (int x = 0; x < d; ++x) cum[r][(size_t)x + 1] = cum[r][(size_t)x] + binom((int64_t)(d - x) + r - 1, r);
+      base[r + 1] = base[r] + binom((int64_t)d + r - 1, r);
+    }
+  }
+};
+
+// The list takes a few ns a feature to build: the rank of (i1, g) is a term of g
+// and two of i1 (symbol by symbol and binomial by binomial it took 0.5 s for the
+// 814,385 features of d = 64, P = 5, now 0.02; the feature table takes 0.04).
 inline StateTable build_state_table(int d, int P, int gt, int it, int zt, bool normalisers, int waves) {
   StateTable st;
   const int m = P - 1, mg = m > 1 ? m - 1 : 1;
-  std::vector<std::vector<uint8_t>> gs;
-  for_each_tuple(d + 1, mg, [&](const int* t) { gs.emplace_back(t, t + mg); });
-  // stable: tuples with one smallest symbol stay in lexicographic order
-  std::stable_sort(gs.begin(), gs.end(),
-                   [](const std::vector<uint8_t>& a, const std::vector<uint8_t>& b) { return a[0] > b[0]; });
+  // the tuples g, one symbol a byte (unused bytes: d): by their smallest symbol,
+  // largest first, then in lexicographic order
+  std::vector<uint64_t> gs;
+  {
+    std::vector<uint64_t> lex;
+    std::vector<size_t> first((size_t)d + 2, 0);  // where the tuples of a smallest symbol start
+    lex.reserve((size_t)binom((int64_t)d + mg, mg));
+    for_each_tuple(d + 1, mg, [&](const int* t) {
+      uint64_t w = 0;
+      for (int j = 0; j < 8; ++j) w |= (uint64_t)(uint8_t)(j < mg ? t[j] : d) << (8 * j);
+      lex.push_back(w);
+      first[(size_t)t[0] + 1] = lex.size();
+    });
+    gs.reserve(lex.size());
+    for (int s = d; s >= 0; --s) gs.insert(gs.end(), lex.begin() + first[(size_t)s], lex.begin() + first[(size_t)s + 1]);
+  }
   const int ng = (int)gs.size();
+  auto symbol = [&](int g, int j) { return (int)(gs[(size_t)g] >> (8 * j) & 0xff); };
   st.gtiles = ((ng + 15) / 16 + gt - 1) / gt * gt;  // whole blocks: kernels read them unchecked
   st.zcols = (d + 1 + 15) / 16 * 16;
-  st.gsym.assign((size_t)st.gtiles * 16, 0);
-  for (int i = 0; i < st.gtiles * 16; ++i) {
-    uint64_t w = 0;
-    for (int j = 0; j < 8; ++j)
-      w |= (uint64_t)(uint8_t)(i < ng && j < mg ? gs[(size_t)i][(size_t)j] : d) << (8 * j);
-    st.gsym[(size_t)i] = w;
+  uint64_t none = 0;
+  for (int j = 0; j < 8; ++j) none |= (uint64_t)(uint8_t)d << (8 * j);
+  st.gsym = gs;
+  st.gsym.resize((size_t)st.gtiles * 16, none);
+  // the part of a feature's rank that is the tuple's, and the tuple's degree
+  const RankSums rs(d);
+  std::vector<int64_t> rank((size_t)ng);
+  std::vector<uint8_t> degree((size_t)ng);
+  for (int g = 0; g < ng; ++g) {
+    int p = mg;
+    while (p > 0 && symbol(g, p - 1) == d) --p;
+    int64_t r = rs.base[p + 1];
+    for (int j = 0; j < p; ++j) {
+      const std::vector<int64_t>& c = rs.cum[p - j - 1];
+      r += c[(size_t)symbol(g, j)] - (j ? c[(size_t)symbol(g, j - 1)] : 0);
+    }
+    rank[(size_t)g] = r;
+    degree[(size_t)g] = (uint8_t)p;
   }
   auto feature = [&](int g, int i1) -> int32_t {
     if (g >= ng) return -1;
-    if (m == 1) {  // the tuples g are the features
-      const int t[1] = {gs[(size_t)g][0]};
-      return i1 == d ? (int32_t)feature_rank(d, t, 1) : -1;
-    }
-    if (i1 > gs[(size_t)g][0]) return -1;
-    int t[kMaxP];
-    t[0] = i1;
-    for (int j = 0; j < mg; ++j) t[j + 1] = gs[(size_t)g][(size_t)j];
-    return (int32_t)feature_rank(d, t, m);
+    const int g0 = symbol(g, 0), p = degree[(size_t)g];
+    if (m == 1) return i1 == d ? (g0 == d ? 0 : 1 + g0) : -1;  // the tuples g are the features
+    if (i1 > g0) return -1;
+    if (i1 == d) return 0;
+    return (int32_t)(rank[(size_t)g] + rs.cum[p][(size_t)i1] - (p > 0 ? rs.cum[p - 1][(size_t)i1] : 0));
   };
   std::vector<StateBlock> low;
   for (int g0 = 0; g0 < st.gtiles; g0 += gt) {
-    const int top = m == 1 ? d : (int)gs[(size_t)g0 * 16][0];  // the largest multiplier of these tiles
+    const int top = m == 1 ? d : symbol(g0 * 16, 0);  // the largest multiplier of these tiles
     for (int i0 = m == 1 ? d : 0; i0 <= top; i0 += it) {
       StateBlock b{g0, i0, std::min(it, top + 1 - i0), 0, (int32_t)st.ftab.size()};
+      st.ftab.resize(st.ftab.size() + (size_t)gt * it * 16, -1);
+      int32_t* f = st.ftab.data() + b.tab;
       for (int t = 0; t < gt; ++t)
         for (int i = 0; i < it; ++i)
-          for (int r = 0; r < 16; ++r) {
-            const int32_t f = i0 + i <= top ? feature((g0 + t) * 16 + r, i0 + i) : -1;
-            st.ftab.push_back(f);
-            if (f >= 0) b.tiles = t + 1;
+          for (int r = 0; r < 16; ++r, ++f) {
+            if (i0 + i <= top) *f = feature((g0 + t) * 16 + r, i0 + i);
+            if (*f >= 0) b.tiles = t + 1;
           }
       (2 * b.rows > it ? st.list : low).push_back(b);
     }

@@ -126,6 +126,36 @@ int main() {
 }
 """
 
+# A first call at new sizes waits for its tables: the work list has to be no
+# longer in the making than a few times the feature table of the same sizes.
+TIME_PROGRAM = r"""
+#include <chrono>
+#include <cstdio>
+#include "state_table.hpp"
+using namespace sata;
+template <typename F> double best(F&& f) {
+  double b = 1e9;
+  for (int i = 0; i < 3; ++i) {
+    const auto t0 = std::chrono::steady_clock::now();
+    f();
+    b = std::min(b, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
+  }
+  return b;
+}
+int main() {
+  int bad = 0;
+  size_t used = 0;
+  for (int i = 0; i < 2; ++i) {
+    const int d = i ? 20 : 64, P = i ? 8 : 5;
+    const double features = best([&] { used += build_gen_program(build_table(d, P), 4096, 32).size(); });
+    const double list = best([&] { used += build_state_table(d, P, state_shape(16, i), 4).ftab.size(); });
+    std::printf("d=%d P=%d: feature table %.4f s, work list %.4f s\n", d, P, features, list);
+    bad += list > 4 * features;
+  }
+  return bad != 0 || used == 0;
+}
+"""
+
 
 def _run(tmp_path, program):
     gxx = shutil.which("g++")
@@ -144,3 +174,7 @@ def test_state_table_holds_every_feature_once(tmp_path):
 
 def test_cached_state_table_is_the_calls_own(tmp_path):
     _run(tmp_path, CACHE_PROGRAM)
+
+
+def test_state_table_is_quick_to_build(tmp_path):
+    _run(tmp_path, TIME_PROGRAM)
