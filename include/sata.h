@@ -28,10 +28,13 @@
  *  - `stream` is a hipStream_t (NULL = the default stream).  Calls are
  *    asynchronous on that stream.  The host waits for the stream in two cases
  *    only: the first call on a device that needs a given (d_k, P) feature
- *    table (it uploads the table and waits for the copy, since every stream of
- *    the device shares it), and a call whose workspace on that stream must grow
- *    (it waits before freeing the smaller one).  A caller that captures calls
- *    into a graph makes one call of each shape first, outside the capture.
+ *    table, or a work list of the pair-by-pair prefill's state (one per d_k, P,
+ *    input type and up to 5 ranges of d_v; it uploads them and waits for the
+ *    copy, since every stream of the device shares them), and a call whose
+ *    workspace on that stream must grow (it waits before freeing the smaller
+ *    one).  A caller that captures calls into a graph makes one call of each
+ *    shape first, outside the capture; a captured call that finds what the scans
+ *    need in place, but not what the pair-by-pair way needs, goes by the scans.
  *  - Arguments are validated on the host before anything is launched; on any
  *    error return nothing has been written and sata_last_error() explains it.
  *  - The library owns only per-device caches (feature tables, workspaces),

@@ -430,6 +430,42 @@ bool backward_direct_pays(sata_dtype dt, int n, int d_k, int d_v, int P, int64_t
   return 1.1 * 1e-3 * pair * (0.5 * n + 256.0) <= scan;
 }
 
+// The pair-by-pair ways allocate and upload other things than the scans (work
+// lists by block shape; scratch for the parts' sums or the statistics), which a
+// capturing stream cannot do.  A call that would have to goes by the scans
+// while its stream is captured: what they need, an earlier call of other sizes
+// may have left.
+bool workspace_holds(hipStream_t stream, size_t bytes) {  // under g_mu
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  auto& spaces = g_devices[dev].workspaces;
+  auto ws = spaces.find(stream);
+  return ws != spaces.end() && ws->second.bytes >= bytes;
+}
+bool prefill_direct_in_place(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int64_t D, bool want_state,
+                             hipStream_t stream) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceCache& dc = g_devices[dev];
+  if (!dc.tables.count(std::make_pair(d_k, P))) return false;
+  if (!want_state) return true;
+  const bool bf16 = dt == SATA_BF16;
+  const auto it = dc.state_tables.find(std::make_tuple(d_k, P, sata::state_shape(d_v, !bf16)));
+  if (it == dc.state_tables.end()) return false;
+  const sata::DevStateTable& st = it->second.dev;
+  const sata::StatePlan plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, (st.blocks + st.zblocks) / 4);
+  return plan.parts == 1 || workspace_holds(stream, plan.partial_bytes);
+}
+bool backward_direct_in_place(int BH, int n, hipStream_t stream) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  return workspace_holds(stream, sata::backward_direct_bytes(BH, n));
+}
+bool captured(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
 // A prefill computed pair by pair: outputs for BH * G query heads, then the
 // state of each of the BH key/value heads as one sum over the tokens.
 sata_status prefill_direct(const void* q, const void* k, const void* v, sata_dtype dt, int BH, int G, int n, int d_k,
@@ -576,10 +612,15 @@ sata_status prefill(Way way, const void* q, const void* k, const void* v, sata_d
   if (n > 0 && (!q || !k || !v || !y)) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
   if (way == Way::kPairs && !direct_covers(n, d_k, d_v, P, D))
     return fail(SATA_ERR_UNSUPPORTED, "no pair-by-pair prefill for n=%d d_k=%d d_v=%d P=%d", n, d_k, d_v, P);
-  if (n > 0 && (way == Way::kPairs ||
-                (way == Way::kEstimate && direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D, S_out != nullptr,
-                                                      vector_rows(q, k, v, dt, d_k, d_v)))))
-    return prefill_direct(q, k, v, dt, B * H_kv, G, n, d_k, d_v, P, y, S_out, (hipStream_t)stream, D);
+  const hipStream_t s = (hipStream_t)stream;
+  const bool want_state = S_out != nullptr;
+  bool pairs = n > 0 && (way == Way::kPairs ||
+                         (way == Way::kEstimate && direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D, want_state,
+                                                               vector_rows(q, k, v, dt, d_k, d_v))));
+  if (pairs && way == Way::kEstimate &&
+      !prefill_direct_in_place(dt, B * H_kv, n, d_k, d_v, P, D, want_state, s) && captured(s))
+    pairs = false;
+  if (pairs) return prefill_direct(q, k, v, dt, B * H_kv, G, n, d_k, d_v, P, y, S_out, s, D);
   const size_t esz = dt == SATA_BF16 ? 2 : 4;
   // query head g + G h of each batch row is member g of key/value head h's
   // group: with the heads of the call numbered by key/value head, member g's
@@ -587,8 +628,7 @@ sata_status prefill(Way way, const void* q, const void* k, const void* v, sata_d
   for (int g = 0; g < G; ++g) {
     const void* qg = (const char*)q + esz * (size_t)g * (size_t)n * (size_t)d_k;
     void* yg = (char*)y + esz * (size_t)g * (size_t)n * (size_t)d_v;
-    st = prefill_dispatch(qg, k, v, dt, B * H_kv, n, d_k, d_v, P, chunk, yg, g == 0 ? S_out : nullptr,
-                          (hipStream_t)stream, D, G);
+    st = prefill_dispatch(qg, k, v, dt, B * H_kv, n, d_k, d_v, P, chunk, yg, g == 0 ? S_out : nullptr, s, D, G);
     if (st != SATA_OK) return st;
     if (n == 0) break;
   }
@@ -624,7 +664,9 @@ sata_status backward(Way way, const void* q, const void* k, const void* v, const
   hipStream_t s = (hipStream_t)stream;
   if (way == Way::kPairs && !backward_direct_covers(n, P))
     return fail(SATA_ERR_UNSUPPORTED, "no pair-by-pair backward for n=%d P=%d", n, P);
-  if (way == Way::kPairs || (way == Way::kEstimate && backward_direct_pays(dt, n, d_k, d_v, P, D))) {
+  bool pairs = way == Way::kPairs || (way == Way::kEstimate && backward_direct_pays(dt, n, d_k, d_v, P, D));
+  if (pairs && way == Way::kEstimate && !backward_direct_in_place(BH, n, s) && captured(s)) pairs = false;
+  if (pairs) {
     void* ws = nullptr;
     if ((st = get_workspace(sata::backward_direct_bytes(BH, n), s, &ws)) != SATA_OK) return st;
     hipError_t e = sata::launch_backward_direct(q, k, v, dy, dq, dk, dv, dt == SATA_BF16, BH, n, d_k, d_v, P,
