@@ -36,6 +36,7 @@
 #include <algorithm>
 
 #include "kernels.hpp"
+#include "route.hpp"
 #include "series.hpp"
 
 namespace sata {
@@ -639,7 +640,7 @@ hipError_t launch_pp(BwdArgs a, hipStream_t s) {
   }
   a.blocks = (a.n + kCh * NQ - 1) / (kCh * NQ);
   a.by_xcd = a.heads >= 8;
-  const unsigned grid = (unsigned)a.blocks * (unsigned)(a.by_xcd ? (a.heads + 7) / 8 * 8 : a.heads);
+  const unsigned grid = (unsigned)pair_blocks(a.heads, a.n, kCh * NQ);
   hipLaunchKernelGGL(rows, dim3(grid), dim3(kNW * 64), L::kBytes, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -649,10 +650,8 @@ hipError_t launch_pp(BwdArgs a, hipStream_t s) {
 
 template <typename T, int DT>
 hipError_t launch_dt(const BwdArgs& a, hipStream_t s) {
-  // Two tiles of own rows per wave share the staged rows' operands; one where
-  // that would leave compute units without work, or (float32) registers short.
   if constexpr (sizeof(T) == 2) {
-    if (((int64_t)a.n + 2 * kCh - 1) / (2 * kCh) * a.heads >= 512)
+    if (backward_tiles(true, a.heads, a.n) == 2)
       return a.P == 4 ? launch_pp<T, DT, 2, 4>(a, s) : launch_pp<T, DT, 2, 0>(a, s);
   }
   return a.P == 4 ? launch_pp<T, DT, 1, 4>(a, s) : launch_pp<T, DT, 1, 0>(a, s);

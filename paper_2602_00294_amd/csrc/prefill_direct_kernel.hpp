@@ -532,7 +532,7 @@ hipError_t launch_p(const void* q, const void* k, const void* v, void* y, int he
   const Series se = make_series(P, dk);
   const int nqb = (n + kCh * NQ - 1) / (kCh * NQ);
   const int by_xcd = heads >= 8;
-  const unsigned grid = (unsigned)nqb * (unsigned)(by_xcd ? (heads + 7) / 8 * 8 : heads);
+  const unsigned grid = (unsigned)pair_blocks(heads, n, kCh * NQ);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kNW * 64), bytes, s, (const T*)q, (const T*)k, (const T*)v, (T*)y, se,
                      heads, qg, n, dk, dv, P, nqb, by_xcd);
   return hipGetLastError();

@@ -42,6 +42,25 @@ inline int direct_query_tiles(bool split, int dv, int heads, int n) {
   return ((int64_t)n + 64 * wide - 1) / (64 * wide) * heads >= 512 ? wide : 1;
 }
 
+// A grid of the pairs' kernels: heads in eights (one per XCD) times blocks of
+// rows.  HIP launches fewer than 2^32 threads, of which a block has 256.
+constexpr int64_t kMaxPairBlocks = ((int64_t)1 << 24) - 1;
+inline int64_t pair_blocks(int heads, int n, int rows_per_block) {
+  return ((int64_t)n + rows_per_block - 1) / rows_per_block * (heads >= 8 ? ((int64_t)heads + 7) / 8 * 8 : heads);
+}
+inline int64_t direct_blocks(bool split, int dv, int query_heads, int n) {
+  return pair_blocks(query_heads, n, 64 * direct_query_tiles(split, dv, query_heads, n));
+}
+// Own rows' tiles per wave of the pair-by-pair backward: two share the staged
+// rows' operands; one where that would leave compute units without work, or
+// (float32) registers short.
+inline int backward_tiles(bool bf16, int heads, int n) {
+  return bf16 && ((int64_t)n + 127) / 128 * heads >= 512 ? 2 : 1;
+}
+inline int64_t backward_blocks(bool bf16, int heads, int n) {
+  return pair_blocks(heads, n, 64 * backward_tiles(bf16, heads, n));
+}
+
 struct RouteCall {
   bool bf16 = false;
   int dk = 0, dv = 0, P = 0;

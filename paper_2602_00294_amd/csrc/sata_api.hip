@@ -365,9 +365,10 @@ PrefillPath prefill_path(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, 
 // offsets into a head's tensor, float32 at d = 64).
 constexpr int64_t kMaxDirectTokens = (int64_t)1 << 22;
 
-// Whether the pair-by-pair prefill covers a shape.
-bool direct_covers(int n, int d_k, int d_v, int P, int64_t D) {
-  return d_k <= 64 && d_v <= 64 && P >= 2 && D <= ((int64_t)1 << 22) && n <= kMaxDirectTokens;
+// Whether the pair-by-pair prefill covers a shape (query heads, for its grid).
+bool direct_covers(sata_dtype dt, int query_heads, int n, int d_k, int d_v, int P, int64_t D) {
+  return d_k <= 64 && d_v <= 64 && P >= 2 && D <= ((int64_t)1 << 22) && n <= kMaxDirectTokens &&
+         sata::direct_blocks(dt == SATA_F32, d_v, query_heads, n) <= sata::kMaxPairBlocks;
 }
 
 // Whether a prefill computes its outputs pair by pair (prefill_direct.hip) and
@@ -375,9 +376,9 @@ bool direct_covers(int n, int d_k, int d_v, int P, int64_t D) {
 // (prefill_state.hip) rather than by the chunked scan: by the estimates of
 // route.hpp.  A grouped call asks for its key/value heads alone: each member is
 // bitwise the single-head prefill of its queries, so both take one way.
-bool direct_pays(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int chunk, int64_t D, bool want_state,
+bool direct_pays(sata_dtype dt, int BH, int G, int n, int d_k, int d_v, int P, int chunk, int64_t D, bool want_state,
                  bool vectors) {
-  if (!direct_covers(n, d_k, d_v, P, D)) return false;
+  if (!direct_covers(dt, BH * G, n, d_k, d_v, P, D)) return false;
   sata::RouteCall r;
   r.bf16 = dt == SATA_BF16;
   r.dk = d_k;
@@ -420,9 +421,11 @@ bool vector_rows(const void* q, const void* k, const void* v, sata_dtype dt, int
 // a share of the state.  Measured, ns per head-token at n = 4096 against the
 // scans: d = 32, P = 4 bf16 3.4 / 206, d = 16, P = 3 bf16 3.1 / 10, d = 16,
 // P = 4 f32 6.0 / 28.5, d = 64, P = 2 f32 20 / 28.
-bool backward_direct_covers(int n, int P) { return P >= 2 && n <= kMaxDirectTokens; }
-bool backward_direct_pays(sata_dtype dt, int n, int d_k, int d_v, int P, int64_t D) {
-  if (!backward_direct_covers(n, P)) return false;
+bool backward_direct_covers(sata_dtype dt, int BH, int n, int P) {
+  return P >= 2 && n <= kMaxDirectTokens && sata::backward_blocks(dt == SATA_BF16, BH, n) <= sata::kMaxPairBlocks;
+}
+bool backward_direct_pays(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int64_t D) {
+  if (!backward_direct_covers(dt, BH, n, P)) return false;
   const int tiles = (std::max(d_k, d_v) + 15) / 16;
   const double pair = (dt == SATA_BF16 ? (tiles <= 2 ? 1.75 : 2.6) : (tiles == 1 ? 3.0 : tiles == 2 ? 3.7 : 10.0)) +
                       0.3 * std::max(0, P - 4);
@@ -610,12 +613,12 @@ sata_status prefill(Way way, const void* q, const void* k, const void* v, sata_d
   sata_status st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D);
   if (st != SATA_OK) return st;
   if (n > 0 && (!q || !k || !v || !y)) return fail(SATA_ERR_INVALID_ARG, "null tensor pointer");
-  if (way == Way::kPairs && !direct_covers(n, d_k, d_v, P, D))
+  if (way == Way::kPairs && !direct_covers(dt, B * H_kv * G, n, d_k, d_v, P, D))
     return fail(SATA_ERR_UNSUPPORTED, "no pair-by-pair prefill for n=%d d_k=%d d_v=%d P=%d", n, d_k, d_v, P);
   const hipStream_t s = (hipStream_t)stream;
   const bool want_state = S_out != nullptr;
   bool pairs = n > 0 && (way == Way::kPairs ||
-                         (way == Way::kEstimate && direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D, want_state,
+                         (way == Way::kEstimate && direct_pays(dt, B * H_kv, G, n, d_k, d_v, P, chunk, D, want_state,
                                                                vector_rows(q, k, v, dt, d_k, d_v))));
   if (pairs && way == Way::kEstimate &&
       !prefill_direct_in_place(dt, B * H_kv, n, d_k, d_v, P, D, want_state, s) && captured(s))
@@ -662,9 +665,9 @@ sata_status backward(Way way, const void* q, const void* k, const void* v, const
   if (!sata::plan_backward(D, BH, n, d_k, d_v, P, chunk, kMaxBackwardWorkspace, &plan, &fwd))
     return fail(SATA_ERR_UNSUPPORTED, "no backward slice fits on chip for d_k=%d d_v=%d chunk=%d", d_k, d_v, chunk);
   hipStream_t s = (hipStream_t)stream;
-  if (way == Way::kPairs && !backward_direct_covers(n, P))
+  if (way == Way::kPairs && !backward_direct_covers(dt, BH, n, P))
     return fail(SATA_ERR_UNSUPPORTED, "no pair-by-pair backward for n=%d P=%d", n, P);
-  bool pairs = way == Way::kPairs || (way == Way::kEstimate && backward_direct_pays(dt, n, d_k, d_v, P, D));
+  bool pairs = way == Way::kPairs || (way == Way::kEstimate && backward_direct_pays(dt, BH, n, d_k, d_v, P, D));
   if (pairs && way == Way::kEstimate && !backward_direct_in_place(BH, n, s) && captured(s)) pairs = false;
   if (pairs) {
     void* ws = nullptr;
@@ -805,7 +808,7 @@ sata_status sata_testing_prefill_route(sata_dtype dt, int B, int H_kv, int G, in
   int64_t D = 0;
   if ((st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D)) != SATA_OK) return st;
   static const sata_route kScans[] = {SATA_ROUTE_MFMA32, SATA_ROUTE_BLOCKS, SATA_ROUTE_FEATURES, SATA_ROUTE_FLOAT32};
-  *route = direct_pays(dt, B * H_kv, n, d_k, d_v, P, chunk, D, want_state != 0,
+  *route = direct_pays(dt, B * H_kv, G, n, d_k, d_v, P, chunk, D, want_state != 0,
                        vector_rows(nullptr, nullptr, nullptr, dt, d_k, d_v))
                ? SATA_ROUTE_PAIRS
                : kScans[(int)prefill_path(dt, B * H_kv, n, d_k, d_v, P, chunk)];
@@ -829,7 +832,7 @@ sata_status sata_testing_backward_route(sata_dtype dt, int B, int H, int n, int 
   int64_t D = 0;
   sata_status st = check_backward_args(dt, B, H, n, d_k, d_v, P, chunk, &D);
   if (st != SATA_OK) return st;
-  *route = backward_direct_pays(dt, n, d_k, d_v, P, D) ? SATA_ROUTE_PAIRS : SATA_ROUTE_FLOAT32;
+  *route = backward_direct_pays(dt, B * H, n, d_k, d_v, P, D) ? SATA_ROUTE_PAIRS : SATA_ROUTE_FLOAT32;
   return ok();
 }
 

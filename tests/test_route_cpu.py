@@ -66,3 +66,17 @@ def test_shapes_without_pairs():
     assert routes.prefill_route("bf16", 1, 64, 16384, 32, 32, 4) == "mfma32"
     with pytest.raises(RuntimeError):
         routes.prefill_route("bf16", 1, 4, 100, 8, 8, 4, chunk=48)
+
+
+@pytest.mark.parametrize("dtype,n", [("f32", 32768), ("bf16", 49152)])
+def test_grids_past_a_launch_go_by_the_scan(dtype, n):
+    """2^24 blocks of 256 threads are one too many for a launch: 65536 heads (in
+    eights) x 256 blocks of 64 x 2 or 3 query rows."""
+    assert routes.prefill_route(dtype, 1, 65535, n - 192, 12, 12, 8) == "pairs"
+    assert routes.prefill_route(dtype, 1, 65535, n, 12, 12, 8) == "features"
+    assert routes.prefill_route(dtype, 1, 8191, n, 12, 12, 8) == "pairs"
+    assert routes.prefill_route(dtype, 1, 8191, n, 12, 12, 8, G=8) == "pairs"        # 65528 query heads: 8 heads fewer
+    assert routes.prefill_route(dtype, 1, 8191, n + 200, 12, 12, 8, G=8) == "features"
+    rows = 16384 if dtype == "f32" else 32768
+    assert routes.backward_route(dtype, 1, 65535, rows - 64, 16, 16, 8) == "pairs"
+    assert routes.backward_route(dtype, 1, 65535, rows, 16, 16, 8) == "float32"
