@@ -78,5 +78,5 @@ def test_grids_past_a_launch_go_by_the_scan(dtype, n):
     assert routes.prefill_route(dtype, 1, 8191, n, 12, 12, 8, G=8) == "pairs"        # 65528 query heads: 8 heads fewer
     assert routes.prefill_route(dtype, 1, 8191, n + 200, 12, 12, 8, G=8) == "features"
     rows = 16384 if dtype == "f32" else 32768
-    assert routes.backward_route(dtype, 1, 65535, rows - 64, 16, 16, 8) == "pairs"
+    assert routes.backward_route(dtype, 1, 65535, rows - 128, 16, 16, 8) == "pairs"
     assert routes.backward_route(dtype, 1, 65535, rows, 16, 16, 8) == "float32"
