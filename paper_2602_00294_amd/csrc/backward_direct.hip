@@ -273,8 +273,9 @@ __device__ __forceinline__ f32x4 (&chunk_sum(f32x4 (&chunk)[DT], f32x4 (&acc)[DT
   }
 }
 template <int PL, int DT>
-__device__ __forceinline__ void add_chunk(const f32x4 (&chunk)[DT], f32x4 (&acc)[DT]) {
+__device__ __forceinline__ void add_chunk(f32x4 (&chunk)[DT], f32x4 (&acc)[DT]) {
   if constexpr (PL > 1) {
+    settle_mfma(chunk);
 #pragma unroll
     for (int j = 0; j < DT; ++j) acc[j] += chunk[j];
   }
@@ -283,6 +284,7 @@ __device__ __forceinline__ void add_chunk(const f32x4 (&chunk)[DT], f32x4 (&acc)
 // lane (l15, g4): columns 16 j + 4 g4 .. +3 of one own row
 template <typename T, int DT>
 __device__ __forceinline__ void store_row(T* p, int width, int g4, const f32x4 (&acc)[DT], float scale) {
+  settle_mfma();
 #pragma unroll
   for (int j = 0; j < DT; ++j)
 #pragma unroll
@@ -393,6 +395,7 @@ __global__ void __launch_bounds__(kNW * 64, sizeof(T) == 2 ? 3 : 2) backward_row
         av[4 * h + r] = y[r];
       }
     }
+    if constexpr (MM == 0) settle_mfma();  // (the series branches on its degree)
   };
   auto masked = [&](int s, float (&x)[8]) {
 #pragma unroll
@@ -561,6 +564,7 @@ backward_cols(BwdArgs a) {
           av[4 * h + r] = y[r];
         }
       }
+      if constexpr (MM == 0) settle_mfma();  // (the series branches on its degree)
       series_eval<MM>(m, u, w, a.se.e, lw);
       series_eval<DM>(m - 1, u, g, a.se.de, ld);
 #pragma unroll

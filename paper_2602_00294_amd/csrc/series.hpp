@@ -143,6 +143,27 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Eight idle cycles between matrix instructions and a branch behind which vector
+// instructions read or overwrite their results.  The result of a 16x16x32 takes
+// that long; the compiler (ROCm 7.2) keeps the distance inside a block of code,
+// but across a branch it was seen to leave 2 and 5 to 7 (three of four rows of
+// dk were stale where it was 2).
+__device__ __forceinline__ void settle_mfma() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 7");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// The same for the results r: what reads them comes after, other code may move.
+template <int N>
+__device__ __forceinline__ void settle_mfma(f32x4 (&r)[N]) {
+  static_assert(N <= 4, "operands of the statement");
+  if constexpr (N == 1) asm volatile("s_nop 7" : "+v"(r[0]));
+  else if constexpr (N == 2) asm volatile("s_nop 7" : "+v"(r[0]), "+v"(r[1]));
+  else if constexpr (N == 3) asm volatile("s_nop 7" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]));
+  else asm volatile("s_nop 7" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+}
+
 // Operand of 8 rows' entries of one column from bf16 rows in LDS, read
 // transposed: p and p + next point at this lane's 8 bytes of the first and the
 // second four rows (lane l of each 16: row l / 4, columns 4 (l % 4) .. +3; it
