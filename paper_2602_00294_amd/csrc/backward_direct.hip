@@ -210,6 +210,15 @@ __device__ __forceinline__ f32x4 dot_rows(const uint4 (&a)[KS][PL], const uint4 
   for (int ks = 0; ks < KS; ++ks) c = dot_planes(a[ks], b[ks], c);
   return c;
 }
+// Scores: with three planes the shift is added to the products' sum (with it first,
+// rounded with at every product, dv of n = 9743, d = 48, P = 3 was 6% further from
+// 64 bits than with the scans, of n = 658, d = 64, P = 2 5%), but for P = 4 of the
+// widest rows, which have no registers for it and are 2 to 4 times nearer than the
+// scans without.
+template <int PL, int DT, int PP>
+constexpr bool shift_last() {
+  return PL > 1 && !(DT == 4 && PP == 4);
+}
 
 // Eight float32 values as three bf16 operands.
 __device__ __forceinline__ void split3(float (&x)[8], uint4 (&b)[3]) {
@@ -281,9 +290,32 @@ __device__ __forceinline__ void add_chunk(f32x4 (&chunk)[DT], f32x4 (&acc)[DT]) 
   }
 }
 
-// lane (l15, g4): columns 16 j + 4 g4 .. +3 of one own row
+// Long sums of float32 dk and dv move on to the output every kFlush chunks, so
+// that their terms are not all rounded at full length (dk of n = 16000, d = 32,
+// P = 4 was 3% further from 64 bits than with the scans; wider rows, which have
+// no registers for it, take few features to the scans before that).
+constexpr int kFlush = 32;
 template <typename T, int DT>
-__device__ __forceinline__ void store_row(T* p, int width, int g4, const f32x4 (&acc)[DT], float scale) {
+constexpr bool flushes() {
+  return sizeof(T) == 4 && DT <= 2;
+}
+template <int DT>
+__device__ __forceinline__ void flush_row(float* p, int width, int g4, f32x4 (&acc)[DT], bool first) {
+#pragma unroll
+  for (int j = 0; j < DT; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = 16 * j + 4 * g4 + r;
+      if (c < width) p[c] = first ? acc[j][r] : p[c] + acc[j][r];
+      acc[j][r] = 0.f;
+    }
+}
+
+// lane (l15, g4): columns 16 j + 4 g4 .. +3 of one own row; `more`: plus what the
+// row holds already
+template <typename T, int DT>
+__device__ __forceinline__ void store_row(T* p, int width, int g4, const f32x4 (&acc)[DT], float scale,
+                                          bool more = false) {
   settle_mfma();
 #pragma unroll
   for (int j = 0; j < DT; ++j)
@@ -291,7 +323,8 @@ __device__ __forceinline__ void store_row(T* p, int width, int g4, const f32x4 (
     for (int r = 0; r < 4; ++r) {
       const int c = 16 * j + 4 * g4 + r;
       if (c < width) {
-        if constexpr (sizeof(T) == 4) p[c] = acc[j][r] * scale;
+        if constexpr (flushes<T, DT>()) p[c] = (more ? p[c] + acc[j][r] : acc[j][r]) * scale;
+        else if constexpr (sizeof(T) == 4) p[c] = acc[j][r] * scale;
         else p[c] = f32_to_bf16(acc[j][r] * scale).bits;
       }
     }
@@ -333,6 +366,7 @@ __global__ void __launch_bounds__(kNW * 64, sizeof(T) == 2 ? 3 : 2) backward_row
   const int n = a.n, dk = a.dk_, dv = a.dv_, m = a.P - 1;
   const float lw = lane < kMaxSeries ? a.se.e[lane & 7] : 0.f, ld = lane < kMaxSeries ? a.se.de[lane & 7] : 0.f;
   constexpr int MM = PP > 0 ? PP - 1 : 0, DM = PP > 1 ? PP - 2 : 0;
+  constexpr bool kLast = shift_last<L::kPl, DT, PP>();
   const T* const qp = (const T*)a.q + (int64_t)head * n * dk;
   const T* const dyp = (const T*)a.dy + (int64_t)head * n * dv;
   RowStage<T, DT> sk, sv;
@@ -385,13 +419,13 @@ __global__ void __launch_bounds__(kNW * 64, sizeof(T) == 2 ? 3 : 2) backward_row
     for (int h = 0; h < 2; ++h) {
       uint4 f[L::kKS][L::kPl];
       load_rows<T, DT>(kb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
-      const f32x4 x = dot_rows(f, qf[I], a.se.shift);
+      const f32x4 x = dot_rows(f, qf[I], kLast ? 0.f : a.se.shift);
       bad |= not_finite(f);
       load_rows<T, DT>(vb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
       const f32x4 y = dot_rows(f, df[I], 0.f);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        u[4 * h + r] = x[r];
+        u[4 * h + r] = kLast ? x[r] + a.se.shift : x[r];
         av[4 * h + r] = y[r];
       }
     }
@@ -501,6 +535,7 @@ backward_cols(BwdArgs a) {
   const int n = a.n, dk = a.dk_, dv = a.dv_, m = a.P - 1;
   const float lw = lane < kMaxSeries ? a.se.e[lane & 7] : 0.f, ld = lane < kMaxSeries ? a.se.de[lane & 7] : 0.f;
   constexpr int MM = PP > 0 ? PP - 1 : 0, DM = PP > 1 ? PP - 2 : 0;
+  constexpr bool kLast = shift_last<L::kPl, DT, PP>();
   const T* const kp = (const T*)a.k + (int64_t)head * n * dk;
   const T* const vp = (const T*)a.v + (int64_t)head * n * dv;
   RowStage<T, DT> sq, sy;
@@ -537,7 +572,7 @@ backward_cols(BwdArgs a) {
   };
   bool dirty = false;  // whether own chunks had entries left out
   // key tile i against the queries of a staged chunk
-  auto work = [&](const u16* base, auto ic, auto own) {
+  auto work = [&](const u16* base, [[maybe_unused]] int c, auto ic, auto own) {
     constexpr int I = decltype(ic)::value;
     constexpr bool kOwn = decltype(own)::value;
     const u16* const qb = base;
@@ -553,14 +588,14 @@ backward_cols(BwdArgs a) {
       for (int h = 0; h < 2; ++h) {
         uint4 f[L::kKS][L::kPl];
         load_rows<T, DT>(qb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
-        const f32x4 x = dot_rows(f, kf[I], a.se.shift);
+        const f32x4 x = dot_rows(f, kf[I], kLast ? 0.f : a.se.shift);
         if (kOwn) bad |= not_finite(f);
         load_rows<T, DT>(yb + (32 * s + 16 * h) * L::kRS, l15, g4, f);
         if (kOwn) bad |= not_finite(f);
         const f32x4 y = dot_rows(f, vf[I], 0.f);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          u[4 * h + r] = x[r];
+          u[4 * h + r] = kLast ? x[r] + a.se.shift : x[r];
           av[4 * h + r] = y[r];
         }
       }
@@ -594,6 +629,16 @@ backward_cols(BwdArgs a) {
     }
     add_chunk<L::kPl>(ck, dka[I]);
     add_chunk<L::kPl>(cv, dva[I]);
+    if constexpr (flushes<T, DT>()) {
+      if ((c - c_first) % kFlush == kFlush - 1) {
+        const int row = (c_first + I) * kCh + 16 * wave + l15;
+        const bool first = c - c_first == kFlush - 1;
+        if (row < n) {
+          flush_row((float*)a.dk + ((int64_t)head * n + row) * dk, dk, g4, dka[I], first);
+          flush_row((float*)a.dv + ((int64_t)head * n + row) * dv, dv, g4, dva[I], first);
+        }
+      }
+    }
   };
   if (c_first < nch) {
     fetch(c_first);
@@ -604,8 +649,8 @@ backward_cols(BwdArgs a) {
       const u16* const base = smem16 + (c & 1) * L::kBuf;
       static_for<NQ>([&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        if (c > c_first + I) work(base, ic, std::false_type{});
-        else if (c == c_first + I) work(base, ic, std::true_type{});
+        if (c > c_first + I) work(base, c, ic, std::false_type{});
+        else if (c == c_first + I) work(base, c, ic, std::true_type{});
       });
       if (c + 1 < nch) put((c + 1) & 1, c + 1);
       __syncthreads();
@@ -625,8 +670,9 @@ backward_cols(BwdArgs a) {
             if (col < dv) dva[i][j][r] += sy.entry(other, col) * 0.f;
           }
     }
-    store_row<T, DT>((T*)a.dk + ((int64_t)head * n + row) * dk, dk, g4, dka[i], 1.f);
-    store_row<T, DT>((T*)a.dv + ((int64_t)head * n + row) * dv, dv, g4, dva[i], 1.f);
+    [[maybe_unused]] const bool more = nch - c_first >= kFlush;
+    store_row<T, DT>((T*)a.dk + ((int64_t)head * n + row) * dk, dk, g4, dka[i], 1.f, more);
+    store_row<T, DT>((T*)a.dv + ((int64_t)head * n + row) * dv, dv, g4, dva[i], 1.f, more);
   }
 }
 
