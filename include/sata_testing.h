@@ -26,7 +26,10 @@ typedef enum {
  * the calls' own validation). */
 sata_status sata_testing_prefill_route(sata_dtype dt, int B, int H_kv, int G, int n, int d_k, int d_v, int P,
                                        int chunk, int want_state, sata_route* route);
-/* The same for sata_backward: SATA_ROUTE_PAIRS, or SATA_ROUTE_FLOAT32 for the scans. */
+/* The scan's kernels for these arguments, whether or not the call goes by them. */
+sata_status sata_testing_scan_route(sata_dtype dt, int B, int H_kv, int n, int d_k, int d_v, int P, int chunk,
+                                    sata_route* route);
+/* The kernels of sata_backward: SATA_ROUTE_PAIRS, or SATA_ROUTE_FLOAT32 for the scans. */
 sata_status sata_testing_backward_route(sata_dtype dt, int B, int H, int n, int d_k, int d_v, int P, int chunk,
                                         sata_route* route);
 

@@ -807,11 +807,22 @@ sata_status sata_testing_prefill_route(sata_dtype dt, int B, int H_kv, int G, in
   if (st != SATA_OK) return st;
   int64_t D = 0;
   if ((st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D)) != SATA_OK) return st;
+  if (direct_pays(dt, B * H_kv, G, n, d_k, d_v, P, chunk, D, want_state != 0,
+                  vector_rows(nullptr, nullptr, nullptr, dt, d_k, d_v))) {
+    *route = SATA_ROUTE_PAIRS;
+    return ok();
+  }
+  return sata_testing_scan_route(dt, B, H_kv, n, d_k, d_v, P, chunk, route);
+}
+
+sata_status sata_testing_scan_route(sata_dtype dt, int B, int H_kv, int n, int d_k, int d_v, int P, int chunk,
+                                    sata_route* route) {
+  if (!route) return fail(SATA_ERR_INVALID_ARG, "null output pointer");
+  int64_t D = 0;
+  sata_status st = check_prefill_args(dt, B, H_kv, n, d_k, d_v, P, chunk, &D);
+  if (st != SATA_OK) return st;
   static const sata_route kScans[] = {SATA_ROUTE_MFMA32, SATA_ROUTE_BLOCKS, SATA_ROUTE_FEATURES, SATA_ROUTE_FLOAT32};
-  *route = direct_pays(dt, B * H_kv, G, n, d_k, d_v, P, chunk, D, want_state != 0,
-                       vector_rows(nullptr, nullptr, nullptr, dt, d_k, d_v))
-               ? SATA_ROUTE_PAIRS
-               : kScans[(int)prefill_path(dt, B * H_kv, n, d_k, d_v, P, chunk)];
+  *route = kScans[(int)prefill_path(dt, B * H_kv, n, d_k, d_v, P, chunk)];
   return ok();
 }
 

@@ -10,6 +10,7 @@ def _lib():
     from paper_2602_00294_amd import _binding
     lib = _binding.load_library()
     lib.sata_testing_prefill_route.argtypes = [_I] * 10 + [ctypes.POINTER(_I)]
+    lib.sata_testing_scan_route.argtypes = [_I] * 8 + [ctypes.POINTER(_I)]
     lib.sata_testing_backward_route.argtypes = [_I] * 8 + [ctypes.POINTER(_I)]
     lib.sata_testing_prefill.argtypes = [_I] + [_VP] * 3 + [_I] * 9 + [_VP] * 3
     lib.sata_testing_backward.argtypes = [_I] + [_VP] * 4 + [_I] * 8 + [_VP] * 4
@@ -30,6 +31,13 @@ def prefill_route(dtype, B, H_kv, n, dk, dv, P, chunk=64, want_state=True, G=1):
     return ROUTES[out.value]
 
 
+def scan_route(dtype, B, H_kv, n, dk, dv, P, chunk=64):
+    """Kernel family of the scan for these sizes, whether or not the call goes by it (host only)."""
+    out = _I(-1)
+    _check(_lib().sata_testing_scan_route(int(dtype == "bf16"), B, H_kv, n, dk, dv, P, chunk, ctypes.byref(out)))
+    return ROUTES[out.value]
+
+
 def backward_route(dtype, B, H, n, dk, dv, P, chunk=64):
     """'pairs' or 'float32' (the scans) for sata.backward (host only)."""
     out = _I(-1)
@@ -46,14 +54,17 @@ def _stream():
     return _VP(torch.cuda.current_stream().cuda_stream)
 
 
-def prefill_by(pairs, q, k, v, P, chunk=64, want_state=True):
-    """prefill (or prefill_grouped, by the head counts) pair by pair or by the scan: (y, S)."""
+def prefill_by(pairs, q, k, v, P, chunk=64, want_state=True, y=None, S=None):
+    """prefill (or prefill_grouped, by the head counts) pair by pair or by the
+    scan: (y, S), preallocated or not."""
     import torch
     B, Hq, n, dk = q.shape
     H, dv = k.shape[1], v.shape[-1]
     from paper_2602_00294_amd import _binding
-    y = torch.empty(B, Hq, n, dv, dtype=q.dtype, device=q.device)
-    S = torch.empty(B, H, _binding.feature_count(dk, P), dv + 1, device=q.device) if want_state else None
+    if y is None:
+        y = torch.empty(B, Hq, n, dv, dtype=q.dtype, device=q.device)
+    if want_state and S is None:
+        S = torch.empty(B, H, _binding.feature_count(dk, P), dv + 1, device=q.device)
     _check(_lib().sata_testing_prefill(int(pairs), _p(q), _p(k), _p(v), int(q.dtype == torch.bfloat16), B, H, Hq // H,
                                        n, dk, dv, P, chunk, _p(y), _p(S), _stream()))
     return y, S

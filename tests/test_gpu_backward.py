@@ -70,6 +70,8 @@ def test_backward_matches_oracle(sata, B, H, n, dk, dv, P, chunk, dtype):
 
 
 def test_backward_chunk_invariance(sata):
+    """(Pair by pair, where the chunk does not matter; the scans' chunks are
+    compared in test_gpu_scan_kernels.py.)"""
     q, k, v = syn.make_qkv(180, 1, 1, 150, 8, 8, "f32")
     dy = syn.make_qkv(181, 1, 1, 150, 8, 8, "f32")[2]
     args = [to_dev(a, "f32") for a in (q, k, v, dy)]

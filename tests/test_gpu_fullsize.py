@@ -124,7 +124,8 @@ def test_large_head_d64(sata):
 
 
 def test_large_head_d64_two_segments(sata):
-    """B=2, H=8, n=10240, d=64, bf16: the generated-feature kernel's partial
+    """B=2, H=8, n=10240, d=64, bf16 (pair by pair by its cost; the scan of these
+    sizes is tested by name elsewhere): the generated-feature kernel's partial
     sums (63 slices x 65 floats per head-token) fill its 2 GB segment at 8192
     tokens, so the state is stored and reloaded once; rows on both sides of
     the boundary and after it, then decode steps from the final state."""

@@ -62,6 +62,7 @@ def _check(got, q, k, v, dy, P, tol, label):
 ])
 def test_pairwise_backward_matches_oracle(sata, B, H, n, dk, dv, P, dtype):
     print(f"pairwise backward B={B} H={H} n={n} dk={dk} dv={dv} P={P} {dtype}", file=sys.stderr, flush=True)
+    assert routes.backward_route(dtype, B, H, n, dk, dv, P) == "pairs"
     q, k, v, dy = _inputs(400 + n, B, H, n, dk, dv, dtype)
     got = [to_host(x) for x in sata.backward(*(to_dev(a, dtype) for a in (q, k, v, dy)), P)]
     torch.cuda.synchronize()
@@ -101,6 +102,7 @@ def test_pairwise_backward_unaligned_rows(sata):
 def test_scan_backward_of_long_sequences(sata, n, dk, dv, P, dtype):
     """Few features and many tokens: the scans over the states."""
     print(f"scan backward n={n} dk={dk} dv={dv} P={P} {dtype}", file=sys.stderr, flush=True)
+    assert routes.backward_route(dtype, 1, 1, n, dk, dv, P) == "float32"
     q, k, v, dy = _inputs(440 + dk, 1, 1, n, dk, dv, dtype)
     if P == 2:  # keep the denominators away from the series' root
         q, k = (_half(a, dtype) for a in (q, k))

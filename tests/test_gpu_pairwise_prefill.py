@@ -1,8 +1,8 @@
 """GPU parity of the prefill computed pair by pair (prefill_direct_kernel.hpp)
 and of the state summed over the tokens (prefill_state.hip) at the edges of
 their tiles, against the float64 oracle, with the bounds of the arithmetic that
-the library reports for the call; and of the scan kernels at the lengths that
-they still serve."""
+the library reports for the call, whatever way the calls' estimated cost would
+take them; and of the scan kernels at lengths that they serve."""
 import math
 import sys
 
@@ -52,7 +52,7 @@ def test_pairwise_prefill_matches_oracle(sata, n, dk, dv, P, dtype):
     print(f"pairwise prefill n={n} dk={dk} dv={dv} P={P} {dtype}", file=sys.stderr, flush=True)
     B, H = 1, 3
     q, k, v = _inputs(500 + n, B, H, n, dk, dv, dtype)
-    y, S = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P)
+    y, S = routes.prefill_by(True, *(to_dev(a, dtype) for a in (q, k, v)), P)
     torch.cuda.synchronize()
     ops = operands(sata, dtype, B, H, n, dk, dv, P, 64)
     for h in range(H):
@@ -69,6 +69,7 @@ def test_pairwise_prefill_matches_oracle(sata, n, dk, dv, P, dtype):
 def test_pairwise_prefill_many_blocks(sata, B, H, n, d, P, dtype):
     """Blocks of several tiles per wave and sequences in parts; sampled heads."""
     print(f"pairwise prefill B={B} H={H} n={n} d={d} P={P} {dtype}", file=sys.stderr, flush=True)
+    assert routes.prefill_route(dtype, B, H, n, d, d, P) == "pairs"
     q, k, v = _inputs(520 + d, B, H, n, d, d, dtype)
     y, S = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P)
     y2, S2 = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P)
@@ -93,7 +94,7 @@ def test_pairwise_prefill_tables_of_both_types(sata, calls, reverse):
         print(f"pairwise prefill tables {dtype} dv={dv}", file=sys.stderr, flush=True)
         q, k, v = _inputs(530, 1, 1, n, dk, dv, dtype)
         S = torch.full((1, 1, oracle.feature_count(dk, P), dv + 1), float("nan"), device="cuda")
-        y, _ = sata.prefill(*(to_dev(a, dtype) for a in (q, k, v)), P, S=S)
+        y, _ = routes.prefill_by(True, *(to_dev(a, dtype) for a in (q, k, v)), P, S=S)
         torch.cuda.synchronize()
         ops = operands(sata, dtype, 1, 1, n, dk, dv, P, 64)
         check_prefill_head(to_host(y)[0, 0], to_host(S)[0, 0], q[0, 0], k[0, 0], v[0, 0], P, ops, dtype, 64,
@@ -113,7 +114,7 @@ def test_pairwise_prefill_unaligned_rows(sata, dtype):
         buf = torch.empty(a.size + 1, device="cuda", dtype=t.dtype)
         buf[1:] = t.reshape(-1)
         dev.append(buf[1:].view(*a.shape))
-    y, S = sata.prefill(*dev[:3], P, y=dev[3])
+    y, S = routes.prefill_by(True, *dev[:3], P, y=dev[3])
     torch.cuda.synchronize()
     ops = operands(sata, dtype, 1, 1, n, dk, dv, P, 64)
     check_prefill_head(to_host(y)[0, 0], to_host(S)[0, 0], *(a[0, 0] for a in arrays), P, ops, dtype, 64, "unaligned")
@@ -126,12 +127,12 @@ def test_pairwise_prefill_keeps_nonfinite_tokens_to_later_chunks(sata, dtype):
     n, d, P = 300, 16, 4
     print(f"pairwise prefill, non-finite tokens {dtype}", file=sys.stderr, flush=True)
     q, k, v = (to_dev(a, dtype) for a in _inputs(550, 1, 1, n, d, d, dtype))
-    y0, _ = sata.prefill(q, k, v, P)
+    y0, _ = routes.prefill_by(True, q, k, v, P)
     bad_k, bad_q = k.clone(), q.clone()
     bad_k[0, 0, 150, 3] = float("nan")
     bad_q[0, 0, 150, 3] = float("nan")
-    yk, _ = sata.prefill(q, bad_k, v, P)
-    yq, _ = sata.prefill(bad_q, k, v, P)
+    yk, _ = routes.prefill_by(True, q, bad_k, v, P)
+    yq, _ = routes.prefill_by(True, bad_q, k, v, P)
     torch.cuda.synchronize()
     assert torch.equal(yk[0, 0, :128], y0[0, 0, :128]) and torch.isnan(yk[0, 0, 150:]).all()
     keep = [t for t in range(n) if t != 150]
@@ -185,16 +186,17 @@ def test_pairwise_prefill_keeps_nonfinite_values_to_their_tile(sata, n, dk, dv, 
     assert torch.isnan(y[..., 2][t[None, :] >= t[:, None]]).all()
 
 
-@pytest.mark.parametrize("B,H,n,d,P,dtype", [
-    (16, 32, 2400, 16, 4, "bf16"),   # the per-block matrix-core kernel
-    (2, 32, 11000, 32, 4, "bf16"),   # the d = 32 matrix-core kernel
-    (8, 32, 2100, 8, 3, "f32"),      # the generated-feature kernel, split operands
-    (8, 32, 4000, 8, 2, "bf16"),     # and with bfloat16 operands
+@pytest.mark.parametrize("B,H,n,d,P,dtype,family", [
+    (16, 32, 4000, 16, 4, "bf16", "blocks"),
+    (2, 32, 20000, 32, 4, "bf16", "mfma32"),
+    (8, 32, 2100, 8, 3, "f32", "features"),     # split operands
+    (8, 32, 6000, 8, 2, "bf16", "features"),
 ])
-def test_scan_prefill_of_long_sequences(sata, B, H, n, d, P, dtype):
+def test_scan_prefill_of_long_sequences(sata, B, H, n, d, P, dtype, family):
     """Sequences long enough for the chunked scan: sampled rows of two heads and
     their whole states."""
     print(f"scan prefill B={B} H={H} n={n} d={d} P={P} {dtype}", file=sys.stderr, flush=True)
+    assert routes.prefill_route(dtype, B, H, n, d, d, P) == routes.scan_route(dtype, B, H, n, d, d, P) == family
     g = torch.Generator(device="cuda").manual_seed(n)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     q, k, v = ((torch.randn(B, H, n, d, generator=g, device="cuda") * s).to(dt) for s in (0.5 ** 0.5, 0.5 ** 0.5, 1.0))

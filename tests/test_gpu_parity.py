@@ -180,7 +180,10 @@ def test_prefill_generated_features_matches_oracle(sata, case):
                                f"{case} b{b} h{h}")
 
 
-# Few heads with few features over a long sequence: the sequence is cut into
+# (These lists go the way that the calls' estimated cost takes them, most of them
+# pair by pair; test_gpu_scan_kernels.py runs them through the scans.)
+
+# Few heads with few features over a long sequence: the scan's sequence is cut into
 # parts that run side by side, each starting from the summed state increments
 # of the parts before it (sata_prefill_parts); every row and the final state
 # against the oracle.
@@ -270,9 +273,9 @@ def test_prefill_chunk_invariance(sata):
 
 @pytest.mark.parametrize("d", [16, 32])
 def test_prefill_chunk_invariance_matrix_cores(sata, d):
-    """bf16, P = 4 on the matrix-core kernels: chunks 32, 64 and 128 (served by
-    different kernel variants) each match the oracle, and agree with each
-    other within the bfloat16-operand bounds."""
+    """bf16, P = 4 on the matrix cores: chunks 32, 64 and 128 each match the
+    oracle, and agree with each other within the bfloat16-operand bounds (pair by
+    pair here; test_gpu_scan_kernels.py compares the scans' variants)."""
     B, H, n, P = 1, 2, 300, 4
     q, k, v = syn.make_qkv(28 + d, B, H, n, d, d, "bf16")
     res = {}
