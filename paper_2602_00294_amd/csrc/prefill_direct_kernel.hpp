@@ -11,11 +11,13 @@
 // issues 16 products of the series, 4 conversions and 2 + NCT matrix
 // instructions, each of which keeps the vector unit from issuing for about 10
 // cycles beside the 16 it runs.  Measured at B = 8, H = 32, n = 8192, d = 32:
-// 1.45 ms (0.17 ps per pair), vector issue busy 89% of the time, against 2.2 ms
-// for the readout half of the scan; 1.90 ms before the chunks were read through
-// buffer descriptors (no tests or 64-bit addresses per vector) and 2.37 ms with
-// V transposed while staging.  Two and four query tiles per wave took 1.54 and
-// 1.53 ms (three: 1.48 in the same run).
+// 1.45 ms (0.17 ps per pair, without a profiler) against 2.2 ms for the readout
+// half of the scan; by the counters vector instructions issue on 73% of a
+// SIMD's cycles and the matrix cores are busy on 43%, with 2.8 waves in flight.
+// 1.90 ms before the chunks were read through buffer descriptors (no tests or
+// 64-bit addresses per vector) and 2.37 ms with V transposed while staging.
+// Two and four query tiles per wave took 1.54 and 1.53 ms (three: 1.48 in the
+// same run).
 //
 // Layout.  The scores are computed transposed, S^T[key][query] = K Q^T, on
 // v_mfma_f32_16x16x32_bf16: the result lane l holds query l % 16 and keys
@@ -538,6 +540,13 @@ hipError_t launch_p(const void* q, const void* k, const void* v, void* y, int he
   return hipGetLastError();
 }
 
+// P = 4, the order of the benchmark's workloads, has its series unrolled; the
+// other orders share one kernel that reads the coefficients from a lane in a
+// loop.  Measured (128 heads, n = 8192, ps per pair, whole call): d = 16
+// bfloat16 P = 2, 3 by the loop 0.109, 0.144, P = 4 unrolled 0.146; float32
+// 0.403, 0.415, 0.401.  So unrolling is worth about a term of the series (0.03
+// to 0.06 ps); an unrolled kernel for each order would be 3.5 times the compiled
+// kernels for that.
 template <typename T, bool X3, bool PK, int NKT, int NCT, int NQ>
 hipError_t launch_one(const void* q, const void* k, const void* v, void* y, int heads, int qg, int n, int dk, int dv,
                       int P, hipStream_t s) {

@@ -14,12 +14,18 @@
 // products) and contracts with [V | 1].  Nothing but the coordinates and V
 // passes through LDS, and the weights enter once, at the end.
 //
-// Bound: vector instructions, 12 per 512 feature-tokens (8 products, 4
-// conversions) beside NCT matrix instructions.  Measured at B = 8, H = 32,
-// n = 8192, d = 32, P = 4 bfloat16: 2.0 ms, 0.96 ns per head-token (the update
-// half of the scan: 2.2 ms); d = 64, B = 2, H = 8, n = 4096: 0.70 ms (the whole
-// scan 3.8).  Tiles one after the other with their multipliers in registers
-// took 2.13 ms where rows of tiles per multiplier took 2.42.
+// Bound: no one unit alone.  Forming 512 feature-tokens takes 8 products and 4
+// conversions beside NCT matrix instructions; with phi_g, staging, normalisers
+// and padded slots the counters show 19 vector and 2.5 matrix instructions
+// (B = 8, H = 32, n = 8192, d = 32, P = 4 bfloat16), vector issue on 55% of a
+// SIMD's cycles (51% at d = 64), matrix cores busy on 25%, and 1.7 waves in
+// flight of the 2 that the registers leave: chunks end at a barrier and
+// workgroups are uneven.  Times, with those before the table entries and
+// weights were fetched ahead of the stores: 1.99 ms (2.14), 0.95 ns per
+// head-token (the update half of the scan: 2.2 ms); B = 64, H = 32, n = 2048,
+// d = 16: 0.89 ms (0.99); B = 2, H = 8, n = 4096, d = 64: 0.58 ms (0.76; the
+// whole scan 3.8).  Tiles one after the other with their multipliers in
+// registers took 2.13 ms where rows of tiles per multiplier took 2.42.
 //
 // Normaliser.  A column of its own for the constant 1 would cost a whole
 // column tile when d_v is a multiple of 16.  There, blocks of their own take

@@ -418,9 +418,12 @@ bool vector_rows(const void* q, const void* k, const void* v, sata_dtype dt, int
 
 // Whether the gradients are computed pair by pair (backward_direct.hip) rather
 // than by the scans over the states: c (n / 2 + 256) ps per head-token against
-// a share of the state.  Measured, ns per head-token at n = 4096 against the
-// scans: d = 32, P = 4 bf16 3.4 / 206, d = 16, P = 3 bf16 3.1 / 10, d = 16,
-// P = 4 f32 6.0 / 28.5, d = 64, P = 2 f32 20 / 28.
+// a share of the state.  Measured, ns per head-token at 128 heads and n = 4096
+// against the scans: bfloat16 d = 16, P = 3 2.9 / 9.8, d = 32, P = 2 3.2 / 12.9,
+// d = 64, P = 2 5.3 / 31; float32 d = 16, P = 3 6.4 / 9.5, d = 32, P = 2
+// 7.8 / 12.5, d = 64, P = 2 20 / 30.  The line errs towards the scans: of 4160
+// calls timed both ways (1 to 1024 heads, 16 to 65536 tokens) it leaves 528 to
+// scans that are slower by 5% and more, and gives none to slower pairs.
 bool backward_direct_covers(sata_dtype dt, int BH, int n, int P) {
   return P >= 2 && n <= kMaxDirectTokens && sata::backward_blocks(dt == SATA_BF16, BH, n) <= sata::kMaxPairBlocks;
 }
