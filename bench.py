@@ -41,7 +41,7 @@ its own line in the same form:
               longest context, far beyond 2^24 tokens, against the oracle
               (Sec. 3.2: cost per token that does not grow with the context);
   backward    B=8, H=32, n=2048, d_k=d_v=32, P=4, bf16: dL/dq, dL/dk, dL/dv
-              (float32 arithmetic), checked on two heads against the oracle;
+              (float32 accuracy), checked on two heads against the oracle;
   decode_grouped B=8, 32 query heads, d_k=d_v=32, P=4, bf16: an 8192-token
               prefill of the key/value heads, then 1024 grouped decode steps
               for G = 2, 4, 8 query heads per key/value head (16, 8, 4
@@ -81,6 +81,38 @@ def prefill_flops_per_head_token(dk, dv, P, C):
     2*d_k (scores) + 2*(d_v+1) (weights times [v|1])."""
     D = feature_count(dk, P)
     return 4 * D * (dv + 1) + (C + 1) * (dk + dv + 1)
+
+
+def pairs_prefill_flops_per_head_token(dk, dv, P, n, state=True):
+    """Work of the prefill pair by pair per head-token: (n+1)/2 keys per query on
+    average, 2*d_k (scores) + 2*(d_v+1) (weights times [v|1]) each, and the sum
+    over tokens that is the state, 2*D*(d_v+1)."""
+    return (n + 1) * (dk + dv + 1) + (2 * feature_count(dk, P) * (dv + 1) if state else 0)
+
+
+def prefill_work(dt, B, H, n, dk, dv, P, C, scan_peak):
+    """(flops, peak TFLOP/s, how) of one sata_prefill call with a state: the work of
+    the kernels that the call takes.  The chunked scan is priced at `scan_peak`;
+    pair by pair, at the bf16 peak, of which float32 inputs as sums of bf16
+    numbers get a share: six products for one of the scores, four for one of the
+    weights times [v|1], three for one of the state."""
+    if not takes_pairs("sata_testing_prefill_route", int(dt == "bf16"), B, H, 1, n, dk, dv, P, C, 1):
+        return prefill_flops_per_head_token(dk, dv, P, C) * B * H * n, scan_peak, "chunked scan"
+    flops = pairs_prefill_flops_per_head_token(dk, dv, P, n)
+    executed = flops if dt == "bf16" else ((n + 1) * (6 * dk + 4 * (dv + 1)) +
+                                           3 * 2 * feature_count(dk, P) * (dv + 1))
+    return flops * B * H * n, PEAK_BF16_TFLOPS * flops / executed, "pair by pair"
+
+
+def takes_pairs(entry, *args):
+    """Whether a call of these sizes goes pair by pair (include/sata_testing.h)."""
+    import ctypes
+
+    from paper_2602_00294_amd import _binding
+    route = ctypes.c_int(-1)
+    if getattr(_binding.load_library(), entry)(*map(ctypes.c_int, args), ctypes.byref(route)):
+        raise RuntimeError(_binding.load_library().sata_last_error().decode())
+    return route.value == 0
 
 
 def decode_bytes_per_head_step(dk, dv, P, elem_bytes):
@@ -279,14 +311,15 @@ def run_workload(args, sata, torch):
         pre_ms = sum(e[0].elapsed_time(e[1]) for e in events) / args.steps
         dec_ms = sum(e[1].elapsed_time(e[2]) for e in events) / args.steps if n_dec else 0.0
         t_total += pre_ms + dec_ms
-        flops = prefill_flops_per_head_token(d, d, Pw, CHUNK) * Bw * Hw * n
-        # on the matrix cores: bf16 operands (bf16 peak), or float32 inputs as
-        # split bf16 pairs (priced at the float32 matrix peak of their dtype)
+        # the scan on the matrix cores: bf16 operands (bf16 peak), or float32 inputs
+        # as split bf16 pairs (priced at the float32 matrix peak of their dtype)
         ops = sata.prefill_operands(tdt, Bw, Hw, n, d, d, Pw, CHUNK)
         mfma = ops in ("bf16", "split")
-        peak = PEAK_BF16_TFLOPS if ops == "bf16" else PEAK_F32_TFLOPS
+        flops, peak, way = prefill_work(dt, Bw, Hw, n, d, d, Pw, CHUNK,
+                                        PEAK_BF16_TFLOPS if ops == "bf16" else PEAK_F32_TFLOPS)
         ach = flops / (pre_ms * 1e-3) / 1e12
-        roof_pre = {"kernel": "sata_prefill (all launches of one call)", "bound": "mfma" if mfma else "alu",
+        roof_pre = {"kernel": f"sata_prefill (all launches of one call, {way})",
+                    "bound": "mfma" if mfma or way == "pair by pair" else "alu",
                     "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak, "traffic": None,
                     "work_per_launch": flops}
         entry = {"prefill_ms": pre_ms, "prefill_tokens_per_s": Bw * n / (pre_ms * 1e-3), "prefill_roofline": roof_pre}
@@ -417,13 +450,14 @@ def run_error_study(args, sata, torch):
         torch.cuda.synchronize()
         ms = ev[0].elapsed_time(ev[-1]) / args.steps
         t_total += ms
-        flops = prefill_flops_per_head_token(d, d, Pw, CHUNK) * n
+        flops, peak, way = prefill_work("f32", 1, 1, n, d, d, Pw, CHUNK, PEAK_F32_TFLOPS)
         ach = flops / (ms * 1e-3) / 1e12
         cells[f"d{d}_P{Pw}"] = {
             "d": d, "P": Pw, "D": feature_count(d, Pw), "prefill_ms": ms, "prefill_tokens_per_s": n / (ms * 1e-3),
-            "prefill_roofline": {"kernel": "sata_prefill (all launches of one call)", "bound": "alu",
-                                 "achieved": ach, "peak": PEAK_F32_TFLOPS, "unit": "TFLOP/s",
-                                 "frac": ach / PEAK_F32_TFLOPS, "traffic": None, "work_per_launch": flops}}
+            "prefill_roofline": {"kernel": f"sata_prefill (all launches of one call, {way})",
+                                 "bound": "mfma" if way == "pair by pair" else "alu",
+                                 "achieved": ach, "peak": peak, "unit": "TFLOP/s",
+                                 "frac": ach / peak, "traffic": None, "work_per_launch": flops}}
         outs[(d, Pw)] = y[0, 0].cpu().numpy()
         del dev, y, S
     worst = min(cells.values(), key=lambda c: c["prefill_roofline"]["frac"])
@@ -570,7 +604,7 @@ CONTEXT_DECODE = 64
 
 
 def backward_flops_per_head_token(dk, dv, P, C):
-    """Algorithmic work of the backward per head-token: the forward readout
+    """Algorithmic work of the backward's scans per head-token: the forward readout
     recomputed (2 D (d_v+1)), the forward scan's S h readout and state update
     (2 x 2 D (d_v+1)), the reverse scan's U [v|1] readout, U^T phi(k) and U
     update (2 D (d_v+1) + 2 D d_v + 2 D (d_v+1)), the two Jacobian products of
@@ -579,6 +613,13 @@ def backward_flops_per_head_token(dk, dv, P, C):
     D = feature_count(dk, P)
     E = dv + 1
     return 2 * D * E + 4 * D * E + (4 * D * E + 2 * D * dv) + 4 * (P - 1) * D + (C + 1) * (3 * dk + 2 * dv + 3)
+
+
+def pairs_backward_flops_per_head_token(dk, dv, n):
+    """Work of the backward pair by pair per head-token: (n+1)/2 pairs on average,
+    scores and dy.v twice for the rows' statistics and dq and once for dk and dv
+    (3 (2 d_k + 2 d_v)), and the contractions for dq, dk and dv (4 d_k + 2 d_v)."""
+    return (n + 1) * (5 * dk + 4 * dv)
 
 
 def run_backward(args, sata, torch):
@@ -605,19 +646,24 @@ def run_backward(args, sata, torch):
     ev[1].record()
     torch.cuda.synchronize()
     ms = ev[0].elapsed_time(ev[1]) / args.steps
-    flops = backward_flops_per_head_token(d, d, Pw, C) * Bw * Hw * n
+    pairs = takes_pairs("sata_testing_backward_route", 1, Bw, Hw, n, d, d, Pw, C)
+    flops = (pairs_backward_flops_per_head_token(d, d, n) if pairs else
+             backward_flops_per_head_token(d, d, Pw, C)) * Bw * Hw * n
+    peak = PEAK_BF16_TFLOPS if pairs else PEAK_F32_TFLOPS
+    way = "pair by pair" if pairs else "chunked scans"
     ach = flops / (ms * 1e-3) / 1e12
     line = {
-        "metric": "backward tokens/s (d_k=32,P=4); % float32 roofline",
+        "metric": f"backward tokens/s (d_k=32,P=4); % {'MFMA' if pairs else 'float32'} roofline",
         "value": Bw * n / (ms * 1e-3), "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": ms, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16",
         "data": "synthetic",
         "config": {"workload": f"backward: dL/dq, dL/dk, dL/dv of the causal prefill, B={Bw} H={Hw} n={n} "
-                               f"d_k=d_v={d} P={Pw} bf16 chunk={C}, float32 arithmetic",
+                               f"d_k=d_v={d} P={Pw} bf16 chunk={C}, float32 accuracy",
                    "global_batch": Bw, "seq_len": n, "heads": Hw, "d_k": d, "d_v": d, "P": Pw, "chunk": C,
                    "parallelism": "single GPU"},
-        "roofline": {"kernel": "sata_backward (all launches of one call)", "bound": "alu", "achieved": ach,
-                     "peak": PEAK_F32_TFLOPS, "unit": "TFLOP/s", "frac": ach / PEAK_F32_TFLOPS, "traffic": None,
+        "roofline": {"kernel": f"sata_backward (all launches of one call, {way})",
+                     "bound": "mfma" if pairs else "alu", "achieved": ach,
+                     "peak": peak, "unit": "TFLOP/s", "frac": ach / peak, "traffic": None,
                      "work_per_launch": flops},
     }
     if not args.no_cpu_baseline:
@@ -866,15 +912,15 @@ def main():
     pre_tok_s = B * N / (pre_ms * 1e-3)
     dec_tok_s = B * args.decode_steps / (dec_ms * 1e-3)
 
-    pre_flops = prefill_flops_per_head_token(DK, DV, P, CHUNK) * B * H * N
+    pre_flops, pre_peak, pre_way = prefill_work("bf16", B, H, N, DK, DV, P, CHUNK, PEAK_BF16_TFLOPS)
     pre_ach = pre_flops / (pre_ms * 1e-3) / 1e12
     dec_bytes = decode_bytes_per_head_step(DK, DV, P, 2) * B * H
     dec_ach = dec_bytes / (dec_ms * 1e-3 / args.decode_steps) / 1e9
     t_y, t_state = measured_traffic("prefill_direct_kernel"), measured_traffic("prefill_state_kernel")
     pre_traffic = t_y + t_state if t_y is not None and t_state is not None else None
-    roof_pre = {"kernel": "sata_prefill (all launches of one call)", "bound": "mfma",
-                "achieved": pre_ach, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                "frac": pre_ach / PEAK_BF16_TFLOPS, "traffic": pre_traffic,
+    roof_pre = {"kernel": f"sata_prefill (all launches of one call, {pre_way})", "bound": "mfma",
+                "achieved": pre_ach, "peak": pre_peak, "unit": "TFLOP/s",
+                "frac": pre_ach / pre_peak, "traffic": pre_traffic,
                 "work_per_launch": pre_flops}
     roof_dec = {"kernel": "sata_decode_step (all launches of one call)", "bound": "hbm",
                 "achieved": dec_ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
