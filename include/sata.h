@@ -33,8 +33,10 @@
  *    copy, since every stream of the device shares them), and a call whose
  *    workspace on that stream must grow (it waits before freeing the smaller
  *    one).  A caller that captures calls into a graph makes one call of each
- *    shape first, outside the capture; a captured call that finds what the scans
- *    need in place, but not what the pair-by-pair way needs, goes by the scans.
+ *    shape first, outside the capture; a captured call whose workspace is too
+ *    small for the parts of its state's sum takes fewer of them, and one that
+ *    finds what the scans need in place, but not what the pair-by-pair way needs,
+ *    goes by the scans.
  *  - Arguments are validated on the host before anything is launched; on any
  *    error return nothing has been written and sata_last_error() explains it.
  *  - The library owns only per-device caches (feature tables, workspaces),

@@ -158,8 +158,9 @@ struct StatePlan {
   int part_len = 0;          // tokens per part
   size_t partial_bytes = 0;  // the parts' states, when parts > 1
 };
-// nwg: workgroups per head of the table (0 before it is known: one part).
-StatePlan plan_prefill_state(int64_t D, int BH, int n, int dv, bool bf16, int nwg);
+// nwg: workgroups per head of the table; scratch: most bytes of the parts' states.
+StatePlan plan_prefill_state(int64_t D, int BH, int n, int dv, bool bf16, int nwg,
+                             size_t scratch = (size_t)512 << 20);
 // The work list of (d_k, P) as the kernel deals it to workgroups.
 StateTable make_state_table(int dk, int P, const StateShape& shape);
 // S_out [BH][D][d_v+1] = the state after n >= 1 tokens; d_k, d_v <= 64, P >= 2.

@@ -593,7 +593,7 @@ hipError_t launch_nct(int nct, const void* k, const void* v, const StateArgs& a,
 
 StateTable make_state_table(int dk, int P, const StateShape& shape) { return build_state_table(dk, P, shape, kNW); }
 
-StatePlan plan_prefill_state(int64_t D, int BH, int n, int dv, bool bf16, int nwg) {
+StatePlan plan_prefill_state(int64_t D, int BH, int n, int dv, bool bf16, int nwg, size_t scratch) {
   StatePlan p;
   p.nct = (dv + 15) / 16;
   p.shape = state_shape(dv, !bf16);
@@ -604,7 +604,7 @@ StatePlan plan_prefill_state(int64_t D, int BH, int n, int dv, bool bf16, int nw
   const size_t state = sizeof(float) * (size_t)BH * D * (dv + 1);
   const int64_t wgs = (int64_t)nwg * BH;
   int parts = 1;
-  while (parts < 64 && wgs * parts * 2 <= 2048 && n / (2 * parts) >= 256 && state * 2 * parts <= ((size_t)512 << 20))
+  while (parts < 64 && wgs * parts * 2 <= 2048 && n / (2 * parts) >= 256 && state * 2 * parts <= scratch)
     parts *= 2;
   if (parts > 1) {
     p.part_len = ((n + parts - 1) / parts + kCh - 1) / kCh * kCh;

@@ -438,34 +438,24 @@ bool backward_direct_pays(sata_dtype dt, int BH, int n, int d_k, int d_v, int P,
 
 // The pair-by-pair ways allocate and upload other things than the scans (work
 // lists by block shape; scratch for the parts' sums or the statistics), which a
-// capturing stream cannot do.  A call that would have to goes by the scans
-// while its stream is captured: what they need, an earlier call of other sizes
-// may have left.
-bool workspace_holds(hipStream_t stream, size_t bytes) {  // under g_mu
+// capturing stream cannot do.  There the state is summed in as many parts as
+// the workspace holds, and a call without its list or statistics goes by the
+// scans: what they need, an earlier call of other sizes may have left.
+size_t workspace_bytes(hipStream_t stream) {
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  std::lock_guard<std::mutex> lock(g_mu);
   auto& spaces = g_devices[dev].workspaces;
   auto ws = spaces.find(stream);
-  return ws != spaces.end() && ws->second.bytes >= bytes;
+  return ws == spaces.end() ? 0 : ws->second.bytes;
 }
-bool prefill_direct_in_place(sata_dtype dt, int BH, int n, int d_k, int d_v, int P, int64_t D, bool want_state,
-                             hipStream_t stream) {
+bool prefill_direct_in_place(sata_dtype dt, int d_k, int d_v, int P, bool want_state) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   std::lock_guard<std::mutex> lock(g_mu);
   DeviceCache& dc = g_devices[dev];
-  if (!dc.tables.count(std::make_pair(d_k, P))) return false;
-  if (!want_state) return true;
-  const bool bf16 = dt == SATA_BF16;
-  const auto it = dc.state_tables.find(std::make_tuple(d_k, P, sata::state_shape(d_v, !bf16)));
-  if (it == dc.state_tables.end()) return false;
-  const sata::DevStateTable& st = it->second.dev;
-  const sata::StatePlan plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, (st.blocks + st.zblocks) / 4);
-  return plan.parts == 1 || workspace_holds(stream, plan.partial_bytes);
-}
-bool backward_direct_in_place(int BH, int n, hipStream_t stream) {
-  std::lock_guard<std::mutex> lock(g_mu);
-  return workspace_holds(stream, sata::backward_direct_bytes(BH, n));
+  return dc.tables.count(std::make_pair(d_k, P)) &&
+         (!want_state || dc.state_tables.count(std::make_tuple(d_k, P, sata::state_shape(d_v, dt != SATA_BF16))));
 }
 bool captured(hipStream_t stream) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -484,10 +474,16 @@ sata_status prefill_direct(const void* q, const void* k, const void* v, sata_dty
   sata::StatePlan plan;
   sata::DevStateTable dst;
   float* partial = nullptr;
+  // (without a state the list is uploaded all the same: a call with one may be
+  // captured after this)
+  if (S_out || (!prefill_direct_in_place(dt, d_k, d_v, P, true) && !captured(s))) {
+    if ((st = get_state_table(d_k, P, sata::state_shape(d_v, !bf16), s, &dst)) != SATA_OK) return st;
+  }
   if (S_out) {
-    plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, 0);
-    if ((st = get_state_table(d_k, P, plan.shape, s, &dst)) != SATA_OK) return st;
-    plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, (dst.blocks + dst.zblocks) / 4);
+    const int nwg = (dst.blocks + dst.zblocks) / 4;
+    plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, nwg);
+    const size_t held = plan.parts > 1 ? workspace_bytes(s) : 0;
+    if (plan.partial_bytes > held && captured(s)) plan = sata::plan_prefill_state(D, BH, n, d_v, bf16, nwg, held);
     if (plan.parts > 1) {
       void* ws = nullptr;
       if ((st = get_workspace(plan.partial_bytes, s, &ws)) != SATA_OK) return st;
@@ -623,8 +619,7 @@ sata_status prefill(Way way, const void* q, const void* k, const void* v, sata_d
   bool pairs = n > 0 && (way == Way::kPairs ||
                          (way == Way::kEstimate && direct_pays(dt, B * H_kv, G, n, d_k, d_v, P, chunk, D, want_state,
                                                                vector_rows(q, k, v, dt, d_k, d_v))));
-  if (pairs && way == Way::kEstimate &&
-      !prefill_direct_in_place(dt, B * H_kv, n, d_k, d_v, P, D, want_state, s) && captured(s))
+  if (pairs && way == Way::kEstimate && !prefill_direct_in_place(dt, d_k, d_v, P, want_state) && captured(s))
     pairs = false;
   if (pairs) return prefill_direct(q, k, v, dt, B * H_kv, G, n, d_k, d_v, P, y, S_out, s, D);
   const size_t esz = dt == SATA_BF16 ? 2 : 4;
@@ -671,7 +666,8 @@ sata_status backward(Way way, const void* q, const void* k, const void* v, const
   if (way == Way::kPairs && !backward_direct_covers(dt, BH, n, P))
     return fail(SATA_ERR_UNSUPPORTED, "no pair-by-pair backward for n=%d P=%d", n, P);
   bool pairs = way == Way::kPairs || (way == Way::kEstimate && backward_direct_pays(dt, BH, n, d_k, d_v, P, D));
-  if (pairs && way == Way::kEstimate && !backward_direct_in_place(BH, n, s) && captured(s)) pairs = false;
+  if (pairs && way == Way::kEstimate && workspace_bytes(s) < sata::backward_direct_bytes(BH, n) && captured(s))
+    pairs = false;
   if (pairs) {
     void* ws = nullptr;
     if ((st = get_workspace(sata::backward_direct_bytes(BH, n), s, &ws)) != SATA_OK) return st;

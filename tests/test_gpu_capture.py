@@ -1,7 +1,7 @@
 """Calls captured into a graph after a warm-up of other sizes: the longer warm-up
 leaves the feature table and a workspace, but not what the pair-by-pair way of
 the shorter call needs, so the captured call goes by the scans; after a warm-up
-of its own it goes pair by pair.  Each graph is replayed several times, with
+of its own it goes pair by pair, and where only scratch is missing too.  Each graph is replayed several times, with
 other inputs and the program's own work in between."""
 import sys
 
@@ -66,6 +66,41 @@ def test_captured_prefill(sata, own_warm_up):
     for want_y, want_S in _replays(graph, stream, held, lambda *x: routes.prefill_by(own_warm_up, *x, P)):
         torch.cuda.synchronize()
         assert torch.equal(y, want_y) and torch.equal(S, want_S)
+
+
+@pytest.mark.parametrize("warm_up", ["no_state", "more_heads"])
+def test_captured_prefill_without_scratch(sata, warm_up):
+    """A warm-up that leaves no scratch for the parts of the state's sum: the same
+    call without a state, or more tokens in all, in heads too short for parts."""
+    n, d, P = 1500, 24, 4
+    assert routes.prefill_route("f32", 1, 2, n, d, d, P) == "pairs"
+    assert routes.prefill_route("f32", 1, 64, 500, d, d, P) == "pairs"
+    print(f"captured prefill, warm-up {warm_up}", file=sys.stderr, flush=True)
+    torch.cuda.synchronize()
+    sata.release()
+    stream = torch.cuda.Stream()
+    held = _tensors(10, n, d, 3)
+    y = torch.empty(1, 2, n, d, device="cuda")
+    S = torch.empty(1, 2, oracle.feature_count(d, P), d + 1, device="cuda")
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        if warm_up == "no_state":
+            sata.prefill(*held, P, y=y, want_state=False)
+        else:
+            many = [t[:, :, :500].repeat(1, 32, 1, 1) for t in held]
+            sata.prefill(*many, P)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        sata.prefill(*held, P, y=y, S=S)
+    for want_y, want_S in _replays(graph, stream, held, lambda *x: routes.prefill_by(True, *x, P)):
+        torch.cuda.synchronize()
+        # y in the same bits; the state's n terms are added in another order, in
+        # float32: at most n 2^-23 of the sum of their sizes
+        sizes = routes.prefill_by(True, held[0], held[1].abs(), held[2].abs(), P)[1]
+        torch.cuda.synchronize()
+        assert torch.equal(y, want_y)
+        assert ((S - want_S).abs() <= n * 2.0 ** -23 * sizes).all()
 
 
 @pytest.mark.parametrize("own_warm_up", [False, True])
